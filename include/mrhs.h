@@ -463,8 +463,9 @@ mrhs_status mrhs_mg_precondition(mrhs_mg mg, void* z, const void* v, int32_t nrh
  * (Sec. 6).  x, b: FP32 device fields [V_level][Nb][nrhs] (x is
  * overwritten; b is read only).  prec: the stencil's arithmetic, MRHS_F32,
  * MRHS_BF16 or MRHS_F16; with BF16 on a level of Nb = 32 and at most 1024
- * sites every step is two launches (stencil fused with the previous step's
- * update and the per-site inner products; the step length).  Synchronises. */
+ * sites every step is one launch (stencil fused with the previous step's
+ * length and update and with the partial inner products), or two where the
+ * partial sums are too many for every workgroup to add.  Synchronises. */
 mrhs_status mrhs_coarse_mr_solve(mrhs_mg mg, int32_t level, void* x, const void* b, int32_t nrhs, int32_t iters,
                                  mrhs_prec prec);
 typedef struct {

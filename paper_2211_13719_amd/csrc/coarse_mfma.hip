@@ -30,6 +30,8 @@
 // FP16 operands are first scaled per right-hand side by a power of two,
 // 2^-E with max_k |x| = m 2^E, m in [0.5, 1), and the output is scaled back in
 // FP32; the power of two keeps the scaling exact.
+#include <type_traits>
+
 #include "mg_internal.h"
 #include "rounding.h"
 
@@ -41,6 +43,15 @@ typedef __attribute__((__vector_size__(8 * sizeof(_Float16)))) _Float16 f16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
 constexpr int kNb = 32;
+// Partial sums of an MR step that every workgroup of the next one sums itself,
+// at most kMrMergedRows rows and kMrMergedBytes per column tile; above it a
+// launch of its own does.  Per step (us, own sum / launch): 3^3 x 16 (216 rows)
+// 11.5 / 13.5 at 12 RHS (62 KB), 15.5 / 16.2 at 24 (124 KB), 27.9 / 25.8 at 48
+// (249 KB); 4^3 x 8 (256 rows) 12.9 / 14.7 at 16 (98 KB), 18.0 / 17.6 at 24
+// (147 KB); 4^3 x 16 (512 rows) 24.0 / 19.6 at one RHS already (12 KB, but 16
+// dependent loads per lane).
+constexpr int kMrMergedRows = 256;
+constexpr long kMrMergedBytes = 128 << 10;
 
 __device__ __forceinline__ unsigned short bf16_rne(float f) { return bf16_rne_bits(__float_as_uint(f)); }
 __device__ __forceinline__ unsigned short f16_rne(float f) { return f16_rne_bits(__float_as_uint(f)); }
@@ -61,6 +72,11 @@ struct Op<false> {
     for (int q = 0; q < 8; ++q) v[q] = (__bf16)x[q];
     return v;
   }
+  static __device__ __forceinline__ uint2 cvt4(const float (&x)[4]) {
+    typedef __bf16 h4 __attribute__((ext_vector_type(4)));
+    const h4 v = {(__bf16)x[0], (__bf16)x[1], (__bf16)x[2], (__bf16)x[3]};
+    return __builtin_bit_cast(uint2, v);
+  }
 };
 template <>
 struct Op<true> {
@@ -74,7 +90,22 @@ struct Op<true> {
     for (int q = 0; q < 8; ++q) v[q] = (_Float16)x[q];
     return v;
   }
+  static __device__ __forceinline__ uint2 cvt4(const float (&x)[4]) {
+    typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+    const h4 v = {(_Float16)x[0], (_Float16)x[1], (_Float16)x[2], (_Float16)x[3]};
+    return __builtin_bit_cast(uint2, v);
+  }
 };
+
+// The eight operand values of lanes 0-15 (and 32-47) from four converted by
+// each lane: lane c holds values 0-3 of column c, lane c + 16 values 4-7 of
+// the same column.  Lanes 16-31 and 48-63 get copies (columns past nrhs).
+template <class Vec>
+__device__ __forceinline__ Vec join_halves(uint2 v) {
+  const auto a = __builtin_amdgcn_permlane16_swap(v.x, v.x, false, false);
+  const auto b = __builtin_amdgcn_permlane16_swap(v.y, v.y, false, false);
+  return __builtin_bit_cast(Vec, make_uint4(a[0], b[0], a[1], b[1]));
+}
 
 // Workgroups are dealt round-robin to the 8 XCDs; remap so that every XCD
 // works on one contiguous range of sites (and keeps their neighbours' vectors
@@ -125,33 +156,58 @@ __device__ __forceinline__ bool reduce_waves(f32x16& accR, f32x16& accI) {
   return true;
 }
 
-// Sum of the WV wavefronts' accumulators into wavefront 0 in a fixed order, a
-// halving tree through LDS (wavefront w + h is added into w for h = WV / 2,
-// WV / 4, ..., 1; for WV = 4 that is (0 + 2) + (1 + 3)).  Every thread of the
-// workgroup must call it.
+// Sum of the WV wavefronts' accumulators, scattered over them: wavefront wv
+// gets the accumulator rows r = wv G + q, q < G = 16 / WV.  Every wavefront
+// writes its 32 accumulators to buf once (WV x 2048 floats), as vectors of G
+// that lie lane by lane, so neither the writes nor the reads conflict, and one
+// barrier separates the two.  The partial sums are added as a halving tree
+// (w + h added into w for h = WV / 2, ..., 1; for WV = 4 that is
+// (0 + 2) + (1 + 3)).  Each wavefront then finishes and stores its own rows
+// instead of leaving all of them to the first one (the tree through lane-major
+// LDS rows with all stores by wavefront 0 before: 4^3 x 16 in BF16 11.6 us at
+// 24 RHS and 18.4 at 48, now 10.0 and 13.8).  Every thread of the WV wavefronts
+// must call it, and a barrier must come before buf is used again.
 template <int WV>
-__device__ __forceinline__ void reduce_waves_t(f32x16& accR, f32x16& accI, float (*red)[64][32]) {
-  const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
+__device__ __forceinline__ void reduce_scatter(const f32x16& accR, const f32x16& accI, float* buf, int wv,
+                                               float (&oR)[16 / WV], float (&oI)[16 / WV]) {
+  constexpr int G = 16 / WV;
+  typedef float vecg __attribute__((ext_vector_type(G)));
+  vecg* b = reinterpret_cast<vecg*>(buf);
+  const int l = threadIdx.x & 63;
 #pragma unroll
-  for (int h = WV / 2; h >= 1; h >>= 1) {
-    if (wv >= h && wv < 2 * h) {
+  for (int gr = 0; gr < WV; ++gr) {
+    vecg vr, vi;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        red[wv - h][l][r] = accR[r];
-        red[wv - h][l][16 + r] = accI[r];
-      }
+    for (int q = 0; q < G; ++q) {
+      vr[q] = accR[gr * G + q];
+      vi[q] = accI[gr * G + q];
     }
-    __syncthreads();
-    if (wv < h) {
+    b[((wv * WV + gr) * 2 + 0) * 64 + l] = vr;
+    b[((wv * WV + gr) * 2 + 1) * 64 + l] = vi;
+  }
+  __syncthreads();
+  vecg sr[WV], si[WV];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        accR[r] += red[wv][l][r];
-        accI[r] += red[wv][l][16 + r];
-      }
+  for (int w = 0; w < WV; ++w) {
+    sr[w] = b[((w * WV + wv) * 2 + 0) * 64 + l];
+    si[w] = b[((w * WV + wv) * 2 + 1) * 64 + l];
+  }
+#pragma unroll
+  for (int h = WV / 2; h >= 1; h >>= 1)
+#pragma unroll
+    for (int w = 0; w < h; ++w) {
+      sr[w] += sr[w + h];
+      si[w] += si[w + h];
     }
-    __syncthreads();
+#pragma unroll
+  for (int q = 0; q < G; ++q) {
+    oR[q] = sr[0][q];
+    oI[q] = si[0][q];
   }
 }
+
+// Component (row of the 32 x 32 output) of accumulator r on lane l.
+__device__ __forceinline__ int acc_row(int r, int l) { return 8 * (r >> 2) + 4 * (l >> 5) + (r & 3); }
 
 // Even-odd modes of the stencil kernels (all coarse extents even; a field on
 // one parity is [V/2][Nb][nrhs], entry i the site of that parity among 2i,
@@ -193,23 +249,34 @@ __device__ __forceinline__ int stencil_nbr(const Geom& g, int s, const int (&x)[
 // 32-column tile of the NT tiles the workgroup covers, so a block slice is
 // loaded once for all its right-hand sides.  A unit past the end is computed
 // on a valid unit with zero operands (straight-line loads, no branch).
-// fetch(row, e, t, d) returns the FP32 operand at row `row` (of the input
-// field of direction d), element offset e = j nrhs + column, for tile t.
+// fetch(row, e, t, d) returns what is loaded at row `row` (of the input field
+// of direction d), element offset e = j nrhs + column, for tile t, as a Raw;
+// operand(raw, t) turns it into the FP32 operand.  mid() runs once, between
+// the loads of the first batch and their use.
 // PAIR (with NT = 2): tile 0 holds the even and tile 1 the odd columns of a
 // 64-column group, lane l columns c0 + 2 (l % 32) and the next, so each
 // operand row is one 16-byte load fetch4(row, e, d) of the column pair at
 // element offset e (colc[0] the even column) instead of two 8-byte loads.
-template <bool F16, int WV, int NT, bool PAIR = false, class Fetch, class Fetch4>
+// HALF (with NT = 1, at most 16 right-hand sides): the lanes whose column is
+// 16 or more would read clamped duplicates; instead each column's rows are
+// split over lanes c and c + 16 and the converted operands are joined by a
+// row swap, so a wavefront issues half the loads and conversions (BF16 at 12
+// RHS: 6^4 14.6 -> 11.6 us, 6^3 x 32 65.9 -> 51.0; at 24 RHS, with all loads,
+// 73.6 -> 72.3).  colc[0] is then the column l % 16.
+template <bool F16, int WV, int NT, bool PAIR, bool HALF, class Raw, class Fetch, class Fetch4, class Operand, class Mid>
 __device__ __forceinline__ void stencil_units(const Geom& g, int s, int io, int EOmode, int nrhs, const uint4* Bp,
-                                              int bstride, const int (&colc)[NT], const bool (&colok)[NT],
-                                              const float (&sc)[NT], Fetch&& fetch, Fetch4&& fetch4,
-                                              f32x16 (&accR)[NT], f32x16 (&accI)[NT]) {
+                                              int bstride, int wv, const int (&colc)[NT], const bool (&colok)[NT],
+                                              const float (&sc)[NT], Fetch&& fetch, Fetch4&& fetch4, Operand&& operand,
+                                              Mid&& mid, f32x16 (&accR)[NT], f32x16 (&accI)[NT]) {
   static_assert(!PAIR || NT == 2, "column pairs fill two tiles");
+  static_assert(!HALF || NT == 1, "half columns are for one tile");
+  constexpr int NQ = HALF ? 4 : 8;  // operand rows per lane and unit
   using O = Op<F16>;
   using vec = typename O::vec;
-  // the wavefront index, and with it each unit's direction, is uniform
-  const int l = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int jh = 8 * (l >> 5);
+  // wv, the wavefront index within the site, and with it each unit's
+  // direction is uniform (read with readfirstlane by the caller)
+  const int l = threadIdx.x & 63;
+  const int jh = 8 * (l >> 5) + (HALF ? 4 * ((l >> 4) & 1) : 0);
   int x[4];
   {
     int r = s;
@@ -227,12 +294,15 @@ __device__ __forceinline__ void stencil_units(const Geom& g, int s, int io, int 
   // instead of once per unit (with one tile all of a wavefront's units form
   // one batch; with two tiles batches of three bound the registers, and for
   // column pairs smaller batches buy occupancy: one-unit batches on four
-  // wavefronts measured fastest, 3 wavefronts per SIMD against 2)
-  constexpr int PB = NT == 1 ? KMAX : (PAIR ? (WV == 4 ? 1 : 2) : 3);
+  // wavefronts measured fastest, 3 wavefronts per SIMD against 2).  Operands
+  // made of two fields (the merged MR step) take twice the registers: batches of
+  // three units with one tile (3^3 x 16 at 24 RHS 14.9 us per step, whole
+  // batches 15.5) and of one with two (at 48 RHS 24.7 us, batches of three 31)
+  constexpr int PB = (sizeof(Raw) > sizeof(float2) && !HALF) ? (NT == 1 ? 3 : 1) : NT == 1 ? KMAX : (PAIR ? (WV == 4 ? 1 : 2) : 3);
 #pragma unroll
   for (int k0 = 0; k0 < KMAX; k0 += PB) {
     uint4 br[PB], bi[PB];
-    float2 ev[PB][NT][8];
+    Raw ev[PB][NT][NQ];
     bool live[PB];
 #pragma unroll
     for (int kk = 0; kk < PB; ++kk) {
@@ -258,9 +328,10 @@ __device__ __forceinline__ void stencil_units(const Geom& g, int s, int io, int 
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-          for (int q = 0; q < 8; ++q) ev[kk][t][q] = fetch(ii, (size_t)(kc * 16 + jh + q) * nrhs + colc[t], t, d);
+          for (int q = 0; q < NQ; ++q) ev[kk][t][q] = fetch(ii, (size_t)(kc * 16 + jh + q) * nrhs + colc[t], t, d);
       }
     }
+    if (k0 == 0) mid();
 #pragma unroll
     for (int kk = 0; kk < PB; ++kk) {
       const uint4 b_i = bi[kk];
@@ -271,14 +342,22 @@ __device__ __forceinline__ void stencil_units(const Geom& g, int s, int io, int 
       const vec an = __builtin_bit_cast(vec, nbi);
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
-        float er[8], ei[8];
-        const bool on = live[kk] && colok[t];
+        float er[NQ], ei[NQ];
+        const bool on = live[kk] && (HALF || colok[t]);
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          er[q] = on ? ev[kk][t][q].x * sc[t] : 0.f;
-          ei[q] = on ? ev[kk][t][q].y * sc[t] : 0.f;
+        for (int q = 0; q < NQ; ++q) {
+          const float2 v = operand(ev[kk][t][q], t);
+          er[q] = on ? v.x * sc[t] : 0.f;
+          ei[q] = on ? v.y * sc[t] : 0.f;
         }
-        const vec vr = O::cvt(er), vi = O::cvt(ei);
+        vec vr, vi;
+        if constexpr (HALF) {
+          vr = join_halves<vec>(O::cvt4(er));
+          vi = join_halves<vec>(O::cvt4(ei));
+        } else {
+          vr = O::cvt(er);
+          vi = O::cvt(ei);
+        }
         accR[t] = O::mma(ar, vr, accR[t]);
         accR[t] = O::mma(an, vi, accR[t]);
         accI[t] = O::mma(ar, vi, accI[t]);
@@ -292,14 +371,15 @@ __device__ __forceinline__ void stencil_units(const Geom& g, int s, int io, int 
 // tiles of right-hand sides).
 // EO = 3 (the coarse Schur complement's outer product, all extents even):
 // out = S_p in - H_{p,1-p} in2 on parity p, in on parity p, in2 on 1 - p.
-template <bool F16, int EO, int WV, int NT, bool PAIR = false>
+template <bool F16, int EO, int WV, int NT, bool PAIR = false, bool HALF = false>
 __global__ __launch_bounds__(64 * WV) void coarse_mfma_kernel(Geom g, int nrhs, const uint4* __restrict__ Bp,
                                                               const float2* __restrict__ in, float2* __restrict__ out,
                                                               const float* __restrict__ scale, int nblocks,
                                                               int parity, int bstride,
                                                               const float2* __restrict__ in2 = nullptr) {
-  __shared__ float red[WV / 2][64][32];
-  const int l = threadIdx.x & 63;
+  __shared__ __attribute__((aligned(16))) float red[WV * 2048];
+  constexpr int G = 16 / WV;
+  const int l = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ngroups = (nrhs + 32 * NT - 1) / (32 * NT);
   const long w = xcd_block(nblocks);
   const int nsite = EO ? g.V / 2 : g.V;
@@ -316,7 +396,8 @@ __global__ __launch_bounds__(64 * WV) void coarse_mfma_kernel(Geom g, int nrhs, 
     col[t] = PAIR ? c0 + 2 * (l & 31) + t : c0 + 32 * t + (l & 31);
     colok[t] = col[t] < nrhs;
     colc[t] = colok[t] ? col[t] : (PAIR ? nrhs - 2 + t : nrhs - 1);
-    sc[t] = (F16 && colok[t]) ? scale[col[t]] : 1.0f;
+    if constexpr (HALF) colc[t] = (l & 15) < nrhs ? (l & 15) : nrhs - 1;
+    sc[t] = (F16 && (HALF || colok[t])) ? scale[colc[t]] : 1.0f;
   }
   f32x16 accR[NT], accI[NT];
 #pragma unroll
@@ -324,8 +405,8 @@ __global__ __launch_bounds__(64 * WV) void coarse_mfma_kernel(Geom g, int nrhs, 
     accR[t] = f32x16{};
     accI[t] = f32x16{};
   }
-  stencil_units<F16, WV, NT, PAIR>(
-      g, s, io, EO, nrhs, Bp, bstride, colc, colok, sc,
+  stencil_units<F16, WV, NT, PAIR, HALF, float2>(
+      g, s, io, EO, nrhs, Bp, bstride, wv, colc, colok, sc,
       // EO 3: minus the hop term, read from the second field (the field is
       // selected before the load, so no branch separates the loads)
       [&](int ii, size_t e, int, int d) {
@@ -338,20 +419,21 @@ __global__ __launch_bounds__(64 * WV) void coarse_mfma_kernel(Geom g, int nrhs, 
         const float4 v = *reinterpret_cast<const float4*>((hop ? in2 : in) + (size_t)ii * kNb * nrhs + e);
         return hop ? make_float4(-v.x, -v.y, -v.z, -v.w) : v;
       },
-      accR, accI);
+      [](float2 v, int) { return v; }, [] {}, accR, accI);
+  float oR[NT][G], oI[NT][G];
 #pragma unroll
-  for (int t = 0; t < NT; ++t) reduce_waves_t<WV>(accR[t], accI[t], red);
-  if ((threadIdx.x >> 6) != 0) return;
+  for (int t = 0; t < NT; ++t) {
+    if (t) __syncthreads();
+    reduce_scatter<WV>(accR[t], accI[t], red, wv, oR[t], oI[t]);
+  }
   if constexpr (PAIR) {
     if (!colok[0]) return;
     const float inv0 = F16 ? 1.0f / sc[0] : 1.0f, inv1 = F16 ? 1.0f / sc[1] : 1.0f;
     float4* o = reinterpret_cast<float4*>(out + (size_t)io * kNb * nrhs + col[0]);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int row = 8 * (r >> 2) + 4 * (l >> 5) + (r & 3);
-      o[(size_t)row * nrhs / 2] =
-          make_float4(accR[0][r] * inv0, accI[0][r] * inv0, accR[1][r] * inv1, accI[1][r] * inv1);
-    }
+    for (int q = 0; q < G; ++q)
+      o[(size_t)acc_row(wv * G + q, l) * nrhs / 2] =
+          make_float4(oR[0][q] * inv0, oI[0][q] * inv0, oR[1][q] * inv1, oI[1][q] * inv1);
   } else {
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
@@ -359,10 +441,8 @@ __global__ __launch_bounds__(64 * WV) void coarse_mfma_kernel(Geom g, int nrhs, 
       const float inv = F16 ? 1.0f / sc[t] : 1.0f;  // exact: sc is a power of two
       float2* o = out + (size_t)io * kNb * nrhs + col[t];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = 8 * (r >> 2) + 4 * (l >> 5) + (r & 3);
-        o[(size_t)row * nrhs] = make_float2(accR[t][r] * inv, accI[t][r] * inv);
-      }
+      for (int q = 0; q < G; ++q)
+        o[(size_t)acc_row(wv * G + q, l) * nrhs] = make_float2(oR[t][q] * inv, oI[t][q] * inv);
     }
   }
 }
@@ -376,35 +456,81 @@ __device__ __forceinline__ float2 mr_residual(float2 rv, float2 pv, float ar, fl
   return rn;
 }
 
-// One minimal-residual step on a coarse level with BF16 operands in two
-// launches (paper Sec. 6: the coarsest level is latency-bound, so a step
-// should be as few kernels as possible, not a stencil, two reductions and an
-// update):
+// One minimal-residual step on a coarse level with BF16 operands in one launch
+// (paper Sec. 6: the coarsest level is latency-bound, so a step should be as
+// few kernels as possible, not a stencil, two reductions and an update):
+//   a_{i-1} = <p_{i-1}, r_{i-1}> / ||p_{i-1}||^2  summed by every workgroup from
+//                                     the partial sums of the previous launch
 //   r_i = r_{i-1} - a_{i-1} p_{i-1}   recomputed on the fly wherever the
 //                                     stencil reads it, stored for the own site
 //   x_i = x_{i-1} + a_{i-1} r_{i-1}   own site, in place
 //   p_i = D r_i                       stored
-//   per (site, column): <p_i, r_i> and ||p_i||^2 over the site's Nb rows (FP64),
-//   which a second small launch (mr_site_alpha_kernel) sums over the sites in
-//   a fixed order into a_i = <p_i, r_i> / ||p_i||^2 per column.
+//   per (workgroup, column): <p_i, r_i> and ||p_i||^2 over the Nb rows of its
+//   NS sites (FP64), one row of `part`, read by the next launch (ppart, prows).
+// All of it is a chain of memory latencies, so the loads that do not depend on
+// each other are issued together: the first of the previous partial sums and
+// the stencil's operands (the step length is summed while they arrive), and
+// the own rows of r, p and x before the wavefronts' reduction, after which
+// each wavefront updates and stores its share of the output rows.
+// Summing the step length in every workgroup costs prows x 24 bytes per column
+// and workgroup out of the L2; mr_step_plan() says up to which size that is
+// cheaper than a launch of its own (mr_site_alpha_kernel; then, not MERGED,
+// the length is read from aold).
 // first: step 0, r_0 = rold as given, x untouched.  Fields [V][Nb][nrhs] FP32;
 // rold / pold and rnew / pnew are different buffers (ping-pong across steps).
 // The step is a template parameter: a run-time flag around the operand loads
 // becomes a branch per load, each waiting for the loads before it.
-template <int WV, int NT, bool first>
-__global__ __launch_bounds__(64 * WV) void coarse_mr_step_kernel(
+// Measured per step of a 64-step solve, before (two launches, all loads of the
+// epilogue and all stores on wavefront 0) and now, in us: 3^3 x 16 17.2 -> 11.1
+// at 12 RHS, 17.5 -> 14.5 at 24, 25.3 -> 23.8 at 64; 2^3 x 4 12.5 -> 6.9 at 12;
+// 4^3 x 16 29.3 -> 18.0 at 12.  What is left at 3^3 x 16 and 12 RHS: 7.3 us for
+// a step without p and without a step length, 1.3 for reading p too, 2.5 for
+// the step length.
+struct MrRaw {
+  float2 r, p;
+};
+
+// v + the value of the lane M = 16 or 32 away (the lane with that index bit
+// flipped), the same sum on both, by a row swap in the vector ALU.
+template <int M>
+__device__ __forceinline__ double add_swapped(double v) {
+  const uint2 w = __builtin_bit_cast(uint2, v);
+  uint2 a, b;
+  if constexpr (M == 16) {
+    const auto x = __builtin_amdgcn_permlane16_swap(w.x, w.x, false, false);
+    const auto y = __builtin_amdgcn_permlane16_swap(w.y, w.y, false, false);
+    a = make_uint2(x[0], y[0]);
+    b = make_uint2(x[1], y[1]);
+  } else {
+    const auto x = __builtin_amdgcn_permlane32_swap(w.x, w.x, false, false);
+    const auto y = __builtin_amdgcn_permlane32_swap(w.y, w.y, false, false);
+    a = make_uint2(x[0], y[0]);
+    b = make_uint2(x[1], y[1]);
+  }
+  return __builtin_bit_cast(double, a) + __builtin_bit_cast(double, b);
+}
+
+
+// (two tiles on four wavefronts: a register budget of three wavefronts per
+// SIMD, 42.8 us against 43.6 at 4^3 x 16 and 48 RHS)
+template <int WV, int NT, int NS, bool HALF, bool MERGED, bool first>
+__global__ __launch_bounds__(64 * WV * NS, (WV == 4 && NT == 2 && MERGED) ? 3 : 1) void coarse_mr_step_kernel(
     Geom g, int nrhs, const uint4* __restrict__ Bp, const float2* __restrict__ rold, const float2* __restrict__ pold,
     float2* __restrict__ rnew, float2* __restrict__ pnew, float2* __restrict__ x, const double2* __restrict__ aold,
-    double4* __restrict__ part, int nblocks) {
-  __shared__ float red[WV / 2][64][32];
-  __shared__ double4 dred[64];
-  const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int ngroups = (nrhs + 32 * NT - 1) / (32 * NT);
+    const double* __restrict__ ppart, int prows, double* __restrict__ part, int nblocks) {
+  constexpr int G = 16 / WV, COLS = 32 * NT;
+  __shared__ __attribute__((aligned(16))) float red[NS * WV * 2048];
+  static_assert(sizeof(red) >= WV * NS * COLS * 24, "sums fit the buffer");
+  const int l = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int ns = wave / WV, wv = wave - ns * WV;
+  const int ngroups = (nrhs + COLS - 1) / COLS;
   const long w = xcd_block(nblocks);
-  const long nwork = (long)g.V * ngroups;
-  if (w >= nwork) return;  // whole workgroup
-  const int s = (int)(w / ngroups);
-  const int c0 = (int)(w % ngroups) * 32 * NT;
+  const int nrow = (g.V + NS - 1) / NS;
+  if (w >= (long)nrow * ngroups) return;  // whole workgroup
+  const int row = (int)(w / ngroups);
+  const bool site_ok = row * NS + ns < g.V;
+  const int s = site_ok ? row * NS + ns : g.V - 1;
+  const int c0 = (int)(w % ngroups) * COLS;
   int col[NT], colc[NT];
   bool colok[NT];
   float sc[NT], ar[NT], ai[NT];
@@ -413,10 +539,30 @@ __global__ __launch_bounds__(64 * WV) void coarse_mr_step_kernel(
     col[t] = c0 + 32 * t + (l & 31);
     colok[t] = col[t] < nrhs;
     colc[t] = colok[t] ? col[t] : nrhs - 1;
+    if constexpr (HALF) colc[t] = (l & 15) < nrhs ? (l & 15) : nrhs - 1;
     sc[t] = 1.0f;
-    const double2 a = first ? make_double2(0.0, 0.0) : aold[colc[t]];
+    const double2 a = first || MERGED ? make_double2(0.0, 0.0) : aold[colc[t]];
     ar[t] = (float)a.x;
     ai[t] = (float)a.y;
+  }
+  // the previous step's partial sums: lane (sub, cu) of wavefront `wave` takes
+  // the rows slot, slot + SLOTS, ... of column c0 + cu, slot = wave SUB + sub;
+  // the first PA of them are loaded before anything else, the others PB at a
+  // time
+  constexpr int CW = HALF ? 16 : COLS, SUB = 64 / CW, SLOTS = WV * NS * SUB;
+  constexpr int PA = HALF ? 7 : 2, PB = 6;
+  const int ncol = nrhs - c0 < CW ? nrhs - c0 : CW;
+  const int cu = l & (CW - 1), slot = wave * SUB + l / CW;
+  const bool summing = !first && MERGED && cu < ncol;
+  double pp[PA][3];
+  if (summing) {
+#pragma unroll
+    for (int u = 0; u < PA; ++u) {
+      const int rr = slot + u * SLOTS;
+      const double* q = ppart + ((rr < prows ? rr : prows - 1) * nrhs + c0 + cu) * 3;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) pp[u][c] = q[c];
+    }
   }
   f32x16 accR[NT], accI[NT];
 #pragma unroll
@@ -424,118 +570,203 @@ __global__ __launch_bounds__(64 * WV) void coarse_mr_step_kernel(
     accR[t] = f32x16{};
     accI[t] = f32x16{};
   }
-  stencil_units<false, WV, NT>(g, s, s, 0, nrhs, Bp, 9, colc, colok, sc,
-                               [&](int ii, size_t e, int t, int) {
-                                 const size_t o = (size_t)ii * kNb * nrhs + e;
-                                 const float2 rv = rold[o];
-                                 if constexpr (first) return rv;
-                                 else return mr_residual(rv, pold[o], ar[t], ai[t]);
-                               },
-                               [](int, size_t, int) { return make_float4(0.f, 0.f, 0.f, 0.f); }, accR, accI);
+  // own rows (clamped column): with half columns there are registers to load
+  // them before the matrix products, else before the wavefronts' reduction
+  float2 rv[NT][G], pv[NT][G], xv[NT][G];
+  auto own_rows = [&] {
 #pragma unroll
-  for (int t = 0; t < NT; ++t) reduce_waves_t<WV>(accR[t], accI[t], red);
-  // epilogue on wavefront 0: own-site r_i, x_i, p_i and the partial sums
-  double4 sum[NT];
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
-  for (int t = 0; t < NT; ++t) sum[t] = make_double4(0.0, 0.0, 0.0, 0.0);
-  if (wv == 0) {
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      // the loads of eight rows first (clamped column), then their arithmetic
-      // and stores: interleaved, each load would wait for the stores before
-      // it; eight rows at a time bound the registers
-      const size_t base = (size_t)s * kNb * nrhs + colc[t];
-#pragma unroll
-      for (int h = 0; h < 16; h += 8) {
-        float2 rv[8], pv[8], xv[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const int r = h + q;
-          const size_t o = base + (size_t)(8 * (r >> 2) + 4 * (l >> 5) + (r & 3)) * nrhs;
-          rv[q] = rold[o];
-          if constexpr (!first) {
-            pv[q] = pold[o];
-            xv[q] = x[o];
-          }
-        }
-        if (colok[t]) {
-#pragma unroll
-          for (int q = 0; q < 8; ++q) {
-            const int r = h + q;
-            const size_t o = base + (size_t)(8 * (r >> 2) + 4 * (l >> 5) + (r & 3)) * nrhs;
-            float2 ri = rv[q];
-            if constexpr (!first) {
-              ri = mr_residual(rv[q], pv[q], ar[t], ai[t]);
-              float2 xn = xv[q];
-              xn.x = fmaf(ar[t], rv[q].x, fmaf(-ai[t], rv[q].y, xn.x));
-              xn.y = fmaf(ar[t], rv[q].y, fmaf(ai[t], rv[q].x, xn.y));
-              x[o] = xn;
-              rnew[o] = ri;
-            }
-            const float2 p = make_float2(accR[t][r], accI[t][r]);
-            pnew[o] = p;
-            const double px = p.x, py = p.y, rx = ri.x, ry = ri.y;
-            sum[t].x = fma(px, rx, fma(py, ry, sum[t].x));
-            sum[t].y = fma(px, ry, fma(-py, rx, sum[t].y));
-            sum[t].z = fma(px, px, fma(py, py, sum[t].z));
-          }
+      for (int q = 0; q < G; ++q) {
+        const size_t o = ((size_t)s * kNb + acc_row(wv * G + q, l)) * nrhs + colc[t];
+        rv[t][q] = rold[o];
+        if constexpr (!first) {
+          pv[t][q] = pold[o];
+          xv[t][q] = x[o];
         }
       }
+  };
+  auto step_length = [&] {
+    if constexpr (first || !MERGED) return;
+    double* sum = reinterpret_cast<double*>(red);  // [wavefront][column][3]
+    double v[3] = {0.0, 0.0, 0.0};
+    if (summing) {
+#pragma unroll
+      for (int u = 0; u < PA; ++u)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) v[c] += slot + u * SLOTS < prows ? pp[u][c] : 0.0;
+      for (int r0 = slot + PA * SLOTS; r0 < prows; r0 += PB * SLOTS) {
+        double q[PB][3];
+#pragma unroll
+        for (int u = 0; u < PB; ++u) {
+          const int rr = r0 + u * SLOTS;
+          const double* e = ppart + ((rr < prows ? rr : prows - 1) * nrhs + c0 + cu) * 3;
+#pragma unroll
+          for (int c = 0; c < 3; ++c) q[u][c] = e[c];
+        }
+#pragma unroll
+        for (int u = 0; u < PB; ++u)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) v[c] += r0 + u * SLOTS < prows ? q[u][c] : 0.0;
+      }
     }
-  }
-  // lanes l and l + 32 of wavefront 0 hold the two row halves of a column
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      if constexpr (CW <= 16) v[c] = add_swapped<16>(v[c]);
+      if constexpr (CW <= 32) v[c] = add_swapped<32>(v[c]);
+    }
+    if (l < CW)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) sum[(wave * CW + l) * 3 + c] = v[c];
+    __syncthreads();
+    // every lane adds the wavefronts' sums of its own columns
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      double w[WV * NS][3];
+#pragma unroll
+      for (int q = 0; q < WV * NS; ++q)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) w[q][c] = sum[(q * CW + colc[t] - c0) * 3 + c];
+#pragma unroll
+      for (int h = WV * NS / 2; h >= 1; h >>= 1)
+#pragma unroll
+        for (int q = 0; q < h; ++q)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) w[q][c] += w[q + h][c];
+      ar[t] = w[0][2] > 0.0 ? (float)(w[0][0] / w[0][2]) : 0.f;
+      ai[t] = w[0][2] > 0.0 ? (float)(w[0][1] / w[0][2]) : 0.f;
+    }
+    __syncthreads();  // red is the wavefronts' reduction buffer next
+  };
+  // with the step length at hand r_i is formed as its parts arrive, else both
+  // are kept until mid() has it
+  constexpr bool LATE = MERGED && !first;
+  using Raw = std::conditional_t<LATE, MrRaw, float2>;
+  stencil_units<false, WV, NT, false, HALF, Raw>(
+      g, s, s, 0, nrhs, Bp, 9, wv, colc, colok, sc,
+      [&](int ii, size_t e, int t, int) {
+        const size_t o = (size_t)ii * kNb * nrhs + e;
+        if constexpr (LATE)
+          return MrRaw{rold[o], pold[o]};
+        else if constexpr (first)
+          return rold[o];
+        else
+          return mr_residual(rold[o], pold[o], ar[t], ai[t]);
+      },
+      [](int, size_t, int) { return make_float4(0.f, 0.f, 0.f, 0.f); },
+      [&](const Raw& v, int t) {
+        if constexpr (LATE)
+          return mr_residual(v.r, v.p, ar[t], ai[t]);
+        else
+          return v;
+      },
+      [&] {
+        if constexpr (HALF) own_rows();
+        step_length();
+      },
+      accR, accI);
+  // own rows of r_i, x_i, p_i and the partial sums
+  if constexpr (!HALF) own_rows();
+  double3 sums[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    if (wv == 0 && l >= 32) dred[l - 32] = sum[t];
-    __syncthreads();
-    if (wv == 0 && l < 32 && colok[t]) {
-      const double4 o = dred[l];
-      part[(size_t)s * nrhs + col[t]] =
-          make_double4(sum[t].x + o.x, sum[t].y + o.y, sum[t].z + o.z, 0.0);
+    float oR[G], oI[G];
+    if (t) __syncthreads();
+    reduce_scatter<WV>(accR[t], accI[t], red + ns * WV * 2048, wv, oR, oI);
+    double sx = 0.0, sy = 0.0, sz = 0.0;
+    if (colok[t] && site_ok) {
+#pragma unroll
+      for (int q = 0; q < G; ++q) {
+        const size_t o = ((size_t)s * kNb + acc_row(wv * G + q, l)) * nrhs + colc[t];
+        float2 ri = rv[t][q];
+        if constexpr (!first) {
+          ri = mr_residual(rv[t][q], pv[t][q], ar[t], ai[t]);
+          float2 xn = xv[t][q];
+          xn.x = fmaf(ar[t], rv[t][q].x, fmaf(-ai[t], rv[t][q].y, xn.x));
+          xn.y = fmaf(ar[t], rv[t][q].y, fmaf(ai[t], rv[t][q].x, xn.y));
+          x[o] = xn;
+          rnew[o] = ri;
+        }
+        pnew[o] = make_float2(oR[q], oI[q]);
+        const double px = oR[q], py = oI[q], rx = ri.x, ry = ri.y;
+        sx = fma(px, rx, fma(py, ry, sx));
+        sy = fma(px, ry, fma(-py, rx, sy));
+        sz = fma(px, px, fma(py, py, sz));
+      }
     }
-    __syncthreads();
+    sums[t].x = sx;
+    sums[t].y = sy;
+    sums[t].z = sz;
+  }
+  // per column: the two row halves of a wavefront, then the wavefronts
+  double* sum = reinterpret_cast<double*>(red);  // [wavefront][tile][column][3]
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    sums[t].x = add_swapped<32>(sums[t].x);
+    sums[t].y = add_swapped<32>(sums[t].y);
+    sums[t].z = add_swapped<32>(sums[t].z);
+    if (l < 32) {
+      double* d = sum + ((wave * NT + t) * 32 + l) * 3;
+      d[0] = sums[t].x;
+      d[1] = sums[t].y;
+      d[2] = sums[t].z;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x >= 32) return;
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    double v[WV * NS][3];
+#pragma unroll
+    for (int q = 0; q < WV * NS; ++q)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) v[q][c] = sum[((q * NT + t) * 32 + l) * 3 + c];
+#pragma unroll
+    for (int h = WV * NS / 2; h >= 1; h >>= 1)
+#pragma unroll
+      for (int q = 0; q < h; ++q)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) v[q][c] += v[q + h][c];
+    if (colok[t])
+#pragma unroll
+      for (int c = 0; c < 3; ++c) part[(row * nrhs + col[t]) * 3 + c] = v[0][c];
   }
 }
 
-// Step length of the fused MR step: one workgroup per column sums the
-// per-site partials in a fixed order (strided by thread, then a tree) and
-// writes a = <p, r> / ||p||^2.
-__global__ __launch_bounds__(256) void mr_site_alpha_kernel(const double4* __restrict__ part, int nsite, int nrhs,
+// Step length of the fused MR step from its partial sums [rows][nrhs][3]: one
+// workgroup per column sums the rows in a fixed order (strided by thread, then
+// a tree) and writes a = <p, r> / ||p||^2.
+__global__ __launch_bounds__(256) void mr_site_alpha_kernel(const double* __restrict__ part, int rows, int nrhs,
                                                             double2* __restrict__ anew) {
-  __shared__ double4 red[256];
+  __shared__ double red[3][256];
   const int k = blockIdx.x, t = threadIdx.x;
-  double4 acc = make_double4(0.0, 0.0, 0.0, 0.0);
-  int site = t;
-  for (; site + 3 * 256 < nsite; site += 4 * 256) {
-    double4 v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = part[(size_t)(site + u * 256) * nrhs + k];
+  double acc[3] = {0.0, 0.0, 0.0};
+  for (int row = t; row < rows; row += 4 * 256) {
+    double v[4][3];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      acc.x += v[u].x;
-      acc.y += v[u].y;
-      acc.z += v[u].z;
+      const int rr = row + u * 256 < rows ? row + u * 256 : row;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) v[u][c] = part[(rr * nrhs + k) * 3 + c];
     }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) acc[c] += row + u * 256 < rows ? v[u][c] : 0.0;
   }
-  for (; site < nsite; site += 256) {
-    const double4 v = part[(size_t)site * nrhs + k];
-    acc.x += v.x;
-    acc.y += v.y;
-    acc.z += v.z;
-  }
-  red[t] = acc;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) red[c][t] = acc[c];
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
-    if (t < w) {
-      red[t].x += red[t + w].x;
-      red[t].y += red[t + w].y;
-      red[t].z += red[t + w].z;
-    }
+    if (t < w)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) red[c][t] += red[c][t + w];
     __syncthreads();
   }
   if (t == 0) {
-    const double4 a = red[0];
-    anew[k] = a.z > 0.0 ? make_double2(a.x / a.z, a.y / a.z) : make_double2(0.0, 0.0);
+    const double z = red[2][0];
+    anew[k] = z > 0.0 ? make_double2(red[0][0] / z, red[1][0] / z) : make_double2(0.0, 0.0);
   }
 }
 
@@ -747,30 +978,62 @@ hipError_t launch_column_scale(const void* in, long rows, int nrhs, void* work, 
 
 namespace {
 
-template <bool F16, int WV, int NT, bool PAIR = false>
+template <bool F16, int WV, int NT, bool PAIR = false, bool HALF = false>
 hipError_t launch_stencil_t(const Geom& g, int nrhs, const void* packed, const void* in, void* out, const float* scale,
                             hipStream_t s) {
   const int blocks = (int)((long)g.V * ((nrhs + 32 * NT - 1) / (32 * NT)));
   const int grid = ((blocks + 7) / 8) * 8;
-  hipLaunchKernelGGL((coarse_mfma_kernel<F16, 0, WV, NT, PAIR>), dim3(grid), dim3(64 * WV), 0, s, g, nrhs,
+  hipLaunchKernelGGL((coarse_mfma_kernel<F16, 0, WV, NT, PAIR, HALF>), dim3(grid), dim3(64 * WV), 0, s, g, nrhs,
                      static_cast<const uint4*>(packed), static_cast<const float2*>(in), static_cast<float2*>(out),
                      scale, blocks, 0, 9, nullptr);
   return hipGetLastError();
 }
 
-template <int WV, int NT>
-hipError_t launch_mr_t(const Geom& g, int nrhs, const void* packed, const void* rold, const void* pold, void* rnew,
-                       void* pnew, void* x, const void* aold, void* anew, void* part, int first, hipStream_t s) {
-  const int blocks = (int)((long)g.V * ((nrhs + 32 * NT - 1) / (32 * NT)));
+// How a fused MR step runs on V sites: NS sites per workgroup, one row of
+// partial sums per workgroup, and whether the next launch sums those rows
+// itself.  Two sites per workgroup where that still leaves about 200
+// workgroups halve the rows (3^3 x 16 at 24 RHS 14.9 us per step, one site
+// 16.8); with two column tiles a workgroup has enough to do with one (4^3 x 16
+// at 48 RHS 42.8 us, two sites 44.5).
+struct MrPlan {
+  int ns, rows;
+  bool merged;
+};
+MrPlan mr_step_plan(const Geom& g, int nrhs, int cfg) {
+  const int wv = cfg & 1 ? 8 : 4, cols = cfg & 2 ? 64 : 32;
+  const int ngroups = (nrhs + cols - 1) / cols;
+  MrPlan p;
+  p.ns = wv == 4 && cols == 32 && (g.V / 2) * ngroups >= 192 ? 2 : 1;
+  p.rows = (g.V + p.ns - 1) / p.ns;
+  p.merged = p.rows <= kMrMergedRows && (long)p.rows * (nrhs < cols ? nrhs : cols) * 3 * (long)sizeof(double) <= kMrMergedBytes;
+  return p;
+}
+
+template <int WV, int NT, int NS, bool HALF, bool MERGED>
+hipError_t launch_mr_k(const Geom& g, int nrhs, const MrPlan& pl, const void* packed, const void* rold, const void* pold,
+                       void* rnew, void* pnew, void* x, const void* aold, const void* ppart, void* part, int first,
+                       hipStream_t s) {
+  const int blocks = (int)((long)pl.rows * ((nrhs + 32 * NT - 1) / (32 * NT)));
   const int grid = ((blocks + 7) / 8) * 8;
-  auto k = first ? coarse_mr_step_kernel<WV, NT, true> : coarse_mr_step_kernel<WV, NT, false>;
-  hipLaunchKernelGGL(k, dim3(grid), dim3(64 * WV), 0, s, g, nrhs, static_cast<const uint4*>(packed),
+  auto k = first ? coarse_mr_step_kernel<WV, NT, NS, HALF, MERGED, true>
+                 : coarse_mr_step_kernel<WV, NT, NS, HALF, MERGED, false>;
+  hipLaunchKernelGGL(k, dim3(grid), dim3(64 * WV * NS), 0, s, g, nrhs, static_cast<const uint4*>(packed),
                      static_cast<const float2*>(rold), static_cast<const float2*>(pold), static_cast<float2*>(rnew),
                      static_cast<float2*>(pnew), static_cast<float2*>(x), static_cast<const double2*>(aold),
-                     static_cast<double4*>(part), blocks);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(mr_site_alpha_kernel, dim3(nrhs), dim3(256), 0, s, static_cast<const double4*>(part), g.V, nrhs,
+                     static_cast<const double*>(ppart), pl.rows, static_cast<double*>(part), blocks);
+  return hipGetLastError();
+}
+
+template <int WV, int NT, int NS, bool HALF>
+hipError_t launch_mr_t(const Geom& g, int nrhs, const MrPlan& pl, const void* packed, const void* rold, const void* pold,
+                       void* rnew, void* pnew, void* x, const void* aold, const void* ppart, void* part, int first,
+                       hipStream_t s) {
+  auto l = pl.merged ? launch_mr_k<WV, NT, NS, HALF, true> : launch_mr_k<WV, NT, NS, HALF, false>;
+  return l(g, nrhs, pl, packed, rold, pold, rnew, pnew, x, aold, ppart, part, first, s);
+}
+
+hipError_t launch_mr_alpha_rows(const void* part, int rows, int nrhs, void* anew, hipStream_t s) {
+  hipLaunchKernelGGL(mr_site_alpha_kernel, dim3(nrhs), dim3(256), 0, s, static_cast<const double*>(part), rows, nrhs,
                      static_cast<double2*>(anew));
   return hipGetLastError();
 }
@@ -787,6 +1050,13 @@ hipError_t launch_coarse_mfma(int f16, const Geom& g, int nb, int nrhs, const vo
                               const float* scale, hipStream_t s, int cfg) {
   if (nb != kNb || cfg < 0 || cfg >= kLowpCfgs) return hipErrorInvalidValue;
   if (cfg >= 4 && (nrhs & 1)) cfg -= 2;
+  if (nrhs <= 16) {  // one tile covers all columns: only the wavefront count is left of cfg
+    if (f16)
+      return cfg & 1 ? launch_stencil_t<true, 8, 1, false, true>(g, nrhs, packed, in, out, scale, s)
+                     : launch_stencil_t<true, 4, 1, false, true>(g, nrhs, packed, in, out, scale, s);
+    return cfg & 1 ? launch_stencil_t<false, 8, 1, false, true>(g, nrhs, packed, in, out, scale, s)
+                   : launch_stencil_t<false, 4, 1, false, true>(g, nrhs, packed, in, out, scale, s);
+  }
   if (f16) {
     switch (cfg) {
       case 0: return launch_stencil_t<true, 4, 1>(g, nrhs, packed, in, out, scale, s);
@@ -807,18 +1077,34 @@ hipError_t launch_coarse_mfma(int f16, const Geom& g, int nb, int nrhs, const vo
   }
 }
 
-size_t coarse_mr_part_bytes(long nsite) { return (size_t)nsite * MRHS_MAX_NRHS * sizeof(double4); }
+// Two sets of partial sums: a step reads the previous one's and writes its own.
+size_t coarse_mr_part_bytes(long nsite) { return 2 * (size_t)nsite * MRHS_MAX_NRHS * 3 * sizeof(double); }
 
 hipError_t launch_coarse_mr_step(const Geom& g, int nb, int nrhs, const void* packed, const void* rold, const void* pold,
-                                 void* rnew, void* pnew, void* x, const void* aold, void* anew, void* part, int first,
-                                 int cfg, hipStream_t s) {
-  if (nb != kNb || cfg < 0 || cfg > 3 || nrhs < 1 || nrhs > MRHS_MAX_NRHS) return hipErrorInvalidValue;
-  switch (cfg) {
-    case 0: return launch_mr_t<4, 1>(g, nrhs, packed, rold, pold, rnew, pnew, x, aold, anew, part, first, s);
-    case 1: return launch_mr_t<8, 1>(g, nrhs, packed, rold, pold, rnew, pnew, x, aold, anew, part, first, s);
-    case 2: return launch_mr_t<4, 2>(g, nrhs, packed, rold, pold, rnew, pnew, x, aold, anew, part, first, s);
-    default: return launch_mr_t<8, 2>(g, nrhs, packed, rold, pold, rnew, pnew, x, aold, anew, part, first, s);
-  }
+                                 void* rnew, void* pnew, void* x, void* alpha, void* part, int step, bool last, int cfg,
+                                 hipStream_t s) {
+  if (nb != kNb || cfg < 0 || cfg > 3 || nrhs < 1 || nrhs > MRHS_MAX_NRHS || step < 0) return hipErrorInvalidValue;
+  const MrPlan pl = mr_step_plan(g, nrhs, cfg);
+  const size_t half = coarse_mr_part_bytes(g.V) / 2;
+  char* pc = static_cast<char*>(part) + (step & 1) * half;
+  const char* pp = static_cast<const char*>(part) + ((step + 1) & 1) * half;
+  const int first = step == 0;
+  hipError_t e;
+#define MRHS_MR(WV, NT, NS, HALF) \
+  launch_mr_t<WV, NT, NS, HALF>(g, nrhs, pl, packed, rold, pold, rnew, pnew, x, alpha, pp, pc, first, s)
+  if (nrhs <= 16)
+    e = cfg & 1 ? MRHS_MR(8, 1, 1, true) : pl.ns == 2 ? MRHS_MR(4, 1, 2, true) : MRHS_MR(4, 1, 1, true);
+  else if (cfg == 0)
+    e = pl.ns == 2 ? MRHS_MR(4, 1, 2, false) : MRHS_MR(4, 1, 1, false);
+  else if (cfg == 1)
+    e = MRHS_MR(8, 1, 1, false);
+  else if (cfg == 2)
+    e = MRHS_MR(4, 2, 1, false);
+  else
+    e = MRHS_MR(8, 2, 1, false);
+#undef MRHS_MR
+  if (e == hipSuccess && (last || !pl.merged)) e = launch_mr_alpha_rows(pc, pl.rows, nrhs, alpha, s);
+  return e;
 }
 
 hipError_t launch_mr_finish(void* x, const void* r, const void* p, void* rout, const void* alpha, long rows, int nrhs,
@@ -852,18 +1138,13 @@ hipError_t launch_coarse_mfma_eo(int prec, int eo, int parity, const Geom& g, in
                          bstride);
   } else {
     const auto* b = static_cast<const uint4*>(packed);
-    if (prec == 2 && eo == 1)
-      hipLaunchKernelGGL((coarse_mfma_kernel<true, 1, 4, 1>), grid, dim3(256), 0, s, g, nrhs, b, x, y, scale, blocks,
-                         parity, bstride, nullptr);
-    else if (prec == 2)
-      hipLaunchKernelGGL((coarse_mfma_kernel<true, 2, 4, 1>), grid, dim3(256), 0, s, g, nrhs, b, x, y, scale, blocks,
-                         parity, bstride, nullptr);
-    else if (eo == 1)
-      hipLaunchKernelGGL((coarse_mfma_kernel<false, 1, 4, 1>), grid, dim3(256), 0, s, g, nrhs, b, x, y, scale, blocks,
-                         parity, bstride, nullptr);
-    else
-      hipLaunchKernelGGL((coarse_mfma_kernel<false, 2, 4, 1>), grid, dim3(256), 0, s, g, nrhs, b, x, y, scale, blocks,
-                         parity, bstride, nullptr);
+    // at most 16 columns: the half-column loads of stencil_units
+    const bool half = nrhs <= 16;
+    auto k = prec == 2 ? (eo == 1 ? (half ? coarse_mfma_kernel<true, 1, 4, 1, false, true> : coarse_mfma_kernel<true, 1, 4, 1>)
+                                  : (half ? coarse_mfma_kernel<true, 2, 4, 1, false, true> : coarse_mfma_kernel<true, 2, 4, 1>))
+                       : (eo == 1 ? (half ? coarse_mfma_kernel<false, 1, 4, 1, false, true> : coarse_mfma_kernel<false, 1, 4, 1>)
+                                  : (half ? coarse_mfma_kernel<false, 2, 4, 1, false, true> : coarse_mfma_kernel<false, 2, 4, 1>));
+    hipLaunchKernelGGL(k, grid, dim3(256), 0, s, g, nrhs, b, x, y, scale, blocks, parity, bstride, nullptr);
   }
   return hipGetLastError();
 }
@@ -876,8 +1157,8 @@ hipError_t launch_coarse_schur(int parity, const Geom& g, int nb, int nrhs, cons
   for (int m = 0; m < 4; ++m)
     if (g.L[m] % 2) return hipErrorInvalidValue;
   const int blocks = (int)((long)(g.V / 2) * ((nrhs + 31) / 32));
-  hipLaunchKernelGGL((coarse_mfma_kernel<false, 3, 4, 1>), dim3((unsigned)(((blocks + 7) / 8) * 8)), dim3(256), 0, s,
-                     g, nrhs, static_cast<const uint4*>(packed), static_cast<const float2*>(in),
+  auto k = nrhs <= 16 ? coarse_mfma_kernel<false, 3, 4, 1, false, true> : coarse_mfma_kernel<false, 3, 4, 1>;
+  hipLaunchKernelGGL(k, dim3((unsigned)(((blocks + 7) / 8) * 8)), dim3(256), 0, s, g, nrhs, static_cast<const uint4*>(packed), static_cast<const float2*>(in),
                      static_cast<float2*>(out), nullptr, blocks, parity, 9, static_cast<const float2*>(in2));
   return hipGetLastError();
 }

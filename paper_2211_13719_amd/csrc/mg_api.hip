@@ -665,22 +665,22 @@ mrhs_status mrhs_mg_tune(mrhs_mg mg, const int32_t* nrhs_list, int32_t count) {
         if (s2 == MRHS_OK) s2 = ensure(ctx, r2, fb);
         if (s2 == MRHS_OK) s2 = ensure(ctx, p2, fb);
         if (s2 == MRHS_OK) s2 = ensure(ctx, part, coarse_mr_part_bytes(L.g.V));
-        if (s2 == MRHS_OK) s2 = ensure(ctx, al, 2 * MRHS_MAX_NRHS * 16);
+        if (s2 == MRHS_OK) s2 = ensure(ctx, al, MRHS_MAX_NRHS * 16);
         if (s2 == MRHS_OK) {
           e = hipMemsetAsync(x.p, 0, fb, ctx->stream);
-          if (e == hipSuccess) e = hipMemsetAsync(al.p, 0, 2 * MRHS_MAX_NRHS * 16, ctx->stream);
+          if (e == hipSuccess) e = hipMemsetAsync(al.p, 0, MRHS_MAX_NRHS * 16, ctx->stream);
           if (e == hipSuccess) e = hipMemsetAsync(p2.p, 0, fb, ctx->stream);
+          if (e == hipSuccess) e = hipMemsetAsync(part.p, 0, coarse_mr_part_bytes(L.g.V), ctx->stream);
           float mbest = 1e30f;
           int mcfg = 0;
-          char* a = static_cast<char*>(al.p);
           for (int c = 0; c < 4 && e == hipSuccess; ++c) {
             if ((c & 2) && n <= 32) continue;
             std::vector<float> t;
             for (int rep = 0; rep < 6 && e == hipSuccess; ++rep) {
               e = hipEventRecord(e0, ctx->stream);
               if (e == hipSuccess)
-                e = launch_coarse_mr_step(L.g, L.ncomp, n, L.Bbf16.p, mg->tmpA.p, p2.p, r2.p, mg->tmpB.p, x.p, a,
-                                          a + MRHS_MAX_NRHS * 16, part.p, 0, c, ctx->stream);
+                e = launch_coarse_mr_step(L.g, L.ncomp, n, L.Bbf16.p, mg->tmpA.p, p2.p, r2.p, mg->tmpB.p, x.p,
+                                          al.p, part.p, 1, false, c, ctx->stream);
               if (e == hipSuccess) e = hipEventRecord(e1, ctx->stream);
               if (e == hipSuccess) e = hipEventSynchronize(e1);
               float ms = 0.f;

@@ -89,14 +89,17 @@ hipError_t launch_column_scale(const void* in, long rows, int nrhs, void* work, 
 // 32-column tiles per workgroup (else one)
 hipError_t launch_coarse_mfma(int f16, const Geom& g, int nb, int nrhs, const void* packed, const void* in, void* out,
                               const float* scale, hipStream_t s, int cfg = 0);
-// One fused minimal-residual step with the BF16 stencil (see the kernel;
-// two launches): part holds coarse_mr_part_bytes(V) bytes.
+// Fused minimal-residual step number `step` (0, 1, ...) with the BF16 stencil
+// (see the kernel): one launch, plus one for the step length on the last step
+// or where the partial sums are too many for each workgroup to add.  part
+// holds coarse_mr_part_bytes(V) bytes; alpha (MRHS_MAX_NRHS double2) has the
+// step's length after the last one.
 size_t coarse_mr_part_bytes(long nsite);
 // Levels that take the fused MR step: Nb = 32 and at most this many sites.
 constexpr int kFusedMrMaxSites = 1024;
 hipError_t launch_coarse_mr_step(const Geom& g, int nb, int nrhs, const void* packed, const void* rold, const void* pold,
-                                 void* rnew, void* pnew, void* x, const void* aold, void* anew, void* part, int first,
-                                 int cfg, hipStream_t s);
+                                 void* rnew, void* pnew, void* x, void* alpha, void* part, int step, bool last, int cfg,
+                                 hipStream_t s);
 // x += a r and, if rout is given, rout = r - a p (the end of a fused MR sweep)
 hipError_t launch_mr_finish(void* x, const void* r, const void* p, void* rout, const void* alpha, long rows, int nrhs,
                             hipStream_t s);

@@ -91,7 +91,7 @@ struct SolverState {
   Buffer lb[MRHS_MAX_LEVELS], lx[MRHS_MAX_LEVELS], lr[MRHS_MAX_LEVELS], lp[MRHS_MAX_LEVELS];
   Buffer alpha, part, scl, coef, qn;
   // fused MR steps on small coarse levels: second r and p fields per level
-  // (ping-pong), two alpha arrays and the per-(site, column) partial sums
+  // (ping-pong), the step lengths and two sets of partial sums
   Buffer lr2[MRHS_MAX_LEVELS], lp2[MRHS_MAX_LEVELS];
   Buffer mralpha, mrpart;
   Buffer gpart, gmat, gT;  // column Gram matrix (setup)
@@ -189,7 +189,7 @@ mrhs_status ensure_levels(mrhs_mg mg, SolverState* st, int n) {
     st->n = n;
   }
   if (!st->mrpart.p) {
-    mrhs_status s = ensure(ctx, st->mralpha, 2 * MRHS_MAX_NRHS * 16);
+    mrhs_status s = ensure(ctx, st->mralpha, MRHS_MAX_NRHS * 16);
     if (s == MRHS_OK) s = ensure(ctx, st->mrpart, coarse_mr_part_bytes(kFusedMrMaxSites));
     if (s != MRHS_OK) return s;
   }
@@ -267,25 +267,24 @@ hipError_t residual_level(mrhs_mg mg, int l, void* r, const void* b, const void*
   return e;
 }
 
-// nu MR steps on a small coarse level with BF16 operands, two launches each
-// (fused stencil, update and per-site inner products; step length), then one
-// launch for the last update of x and r.  p and the level's second r / p
-// fields are overwritten.
+// nu MR steps on a small coarse level with BF16 operands, one launch each
+// (stencil, previous update and step length, partial inner products) where the
+// partial sums are few, then the last step's length and one launch for its
+// update of x and r.  p and the level's second r / p fields are overwritten.
 hipError_t mr_steps_fused(mrhs_mg mg, SolverState* st, int l, void* x, void* r, void* p, int n, int nu) {
   if (nu <= 0) return hipSuccess;
   LevelData& L = mg->lv[l];
   void* R[2] = {r, st->lr2[l].p};
   void* P[2] = {p, st->lp2[l].p};
-  char* a = static_cast<char*>(st->mralpha.p);
-  void* A[2] = {a, a + MRHS_MAX_NRHS * 16};
+  void* alpha = st->mralpha.p;
   for (int i = 0; i < nu; ++i) {
     const int cur = i & 1, prv = (i + 1) & 1;
     hipError_t e = launch_coarse_mr_step(L.g, L.ncomp, n, L.Bbf16.p, i == 0 ? R[0] : R[prv], P[prv], R[cur], P[cur],
-                                         x, A[prv], A[cur], st->mrpart.p, i == 0, L.mr_cfg[n], st->stream);
+                                         x, alpha, st->mrpart.p, i, i == nu - 1, L.mr_cfg[n], st->stream);
     if (e != hipSuccess) return e;
   }
   const int last = (nu - 1) & 1;
-  return launch_mr_finish(x, R[last], P[last], r, A[last], level_rows(mg, l), n, st->stream);
+  return launch_mr_finish(x, R[last], P[last], r, alpha, level_rows(mg, l), n, st->stream);
 }
 
 // nu MR steps on D_l x = b with x and r = b - D x kept up to date.

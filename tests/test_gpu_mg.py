@@ -479,6 +479,71 @@ def test_coarse_mr_solve_vs_emulation(gpu_lib, cdims, cfg, prec):
                     assert torch.equal(x, x2)
 
 
+@pytest.mark.parametrize("cdims,nrhs", [
+    ((1, 1, 1, 1), 1), ((2, 2, 1, 3), 16), ((2, 2, 1, 3), 17), ((3, 3, 3, 15), 1), ((3, 3, 3, 15), 15),
+    ((3, 3, 3, 15), 20), ((3, 3, 3, 15), 33), ((4, 4, 4, 9), 16), ((4, 4, 4, 9), 18), ((4, 4, 4, 9), 33),
+])
+def test_coarse_mr_solve_step_forms(gpu_lib, cdims, nrhs):
+    """The forms of the fused MR step at their edges: half-column loads up to 16
+    RHS, one or two sites per workgroup (an odd count leaves half of the last
+    one empty), the step length summed by the next launch (up to 256 rows of
+    partial sums) or by one of its own.  Against the emulation of
+    test_coarse_mr_solve_vs_emulation with its bars (one step 1e-5, more steps
+    2e-3), for both wavefront counts, and bit for bit on a second call."""
+    import torch
+
+    nb = 32
+    ctx, mg = coarse_mg(gpu_lib, cdims, nb)
+    Vc = synth.volume(cdims)
+    B = synth.gaussian_blocks(Vc, nb, 47, shift=24.0)
+    mg.set_blocks(1, B)
+    b = synth.coarse_source(Vc, nb, nrhs, 53, np.complex64)
+    for iters, tol in ((1, 1e-5), (4, 2e-3)):
+        want = _mr_ref(B, b, cdims, iters, "bf16")
+        for cfg in (0, 1, 2, 3):
+            mg.set_lowp_cfg(1, nrhs, cfg)
+            x, x2 = (torch.empty((Vc, nb, nrhs), dtype=torch.complex64, device="cuda") for _ in range(2))
+            mg.coarse_mr_solve(1, x, dev(b), iters, "bf16")
+            mg.coarse_mr_solve(1, x2, dev(b), iters, "bf16")
+            assert rel(host(x), want) < tol, (iters, cfg, rel(host(x), want))
+            assert torch.equal(x, x2)
+
+
+@pytest.mark.parametrize("nrhs", [1, 15, 16, 17])
+@pytest.mark.parametrize("fmt", ["bf16", "f16"])
+def test_coarse_half_column_loads(gpu_lib, nrhs, fmt):
+    """Up to 16 RHS the BF16/FP16 stencil splits each column's rows over two
+    lanes: full, hop and self modes against the oracle on the rounded operands
+    (1e-6) around the switch, for both wavefront counts of the full stencil."""
+    import torch
+
+    cdims, nb = (2, 4, 2, 6), 32
+    ctx, mg = coarse_mg(gpu_lib, cdims, nb)
+    Vc = synth.volume(cdims)
+    B = synth.gaussian_blocks(Vc, nb, 59)
+    mg.set_blocks(1, B)
+    e = synth.coarse_source(Vc, nb, nrhs, 61, np.complex64)
+    want = O.coarse_apply_lowprec(B, e, cdims, fmt)
+    for cfg in (0, 1):
+        mg.set_lowp_cfg(1, nrhs, cfg)
+        o = torch.empty((Vc, nb, nrhs), dtype=torch.complex64, device="cuda")
+        mg.coarse_apply(1, o, dev(e), fmt)
+        assert rel(host(o), want) < 1e-6, cfg
+    # hop from parity 1 plus self on parity 0 of a field living on both: the full stencil's even rows
+    site = np.arange(Vc)
+    par, r = np.zeros(Vc, dtype=int), site.copy()
+    for L in cdims:
+        par += r % L
+        r //= L
+    par &= 1
+    ev, od = np.flatnonzero(par == 0), np.flatnonzero(par == 1)
+    hop, own = (torch.empty((Vc // 2, nb, nrhs), dtype=torch.complex64, device="cuda") for _ in range(2))
+    mg.coarse_hop_eo(1, hop, dev(np.ascontiguousarray(e[od])), 0, fmt)
+    mg.coarse_self_eo(1, own, dev(np.ascontiguousarray(e[ev])), 0, False, fmt)
+    # FP16 scales are powers of two per field, so the operands round as in the full apply
+    assert rel(host(hop) + host(own), want[ev]) < 1e-6
+
+
 def test_coarse_apply_nb8_valu(gpu_lib):
     import torch
 
