@@ -180,6 +180,40 @@ def test_restrict_prolong_bf16(gpu_lib, nrhs):
         assert rel(got, O.prolong(b32, yc, d, blocks[lev])) < 2e-2
 
 
+@pytest.mark.parametrize("dims,block,level", [
+    ((4, 4, 4, 4), (2, 2, 2, 2), 0),    # 16 sites: one tile, prolongation in one part
+    ((4, 6, 4, 6), (4, 2, 2, 3), 0),    # 48 sites: an odd number of tiles, 12 aggregates over 8 XCDs
+    ((12, 12, 8, 8), (4, 4, 4, 4), 0),  # 36 aggregates: every restriction staged
+    ((4, 4, 6, 4), (2, 2, 2, 2), 1),    # step 1: 32 components of the 16-site aggregates of a coarse level
+])
+@pytest.mark.parametrize("nrhs", [1, 4, 16, 17, 31, 33, 63])
+def test_restrict_prolong_tiles(gpu_lib, dims, block, level, nrhs):
+    """The tiled matrix-core transfers at the edges of their tiles (sites per
+    aggregate, odd column counts, one and two column tiles) and where they
+    leave the shape to the other kernels; FP32 and BF16 as in the tests above."""
+    import torch
+
+    blocks = [block] if level == 0 else [(2, 2, 2, 2), block]
+    fine = dims if level == 0 else tuple(2 * d for d in dims)
+    ctx, mg = make_mg(gpu_lib, fine, blocks, [16] * len(blocks))
+    V, nc = mg.volume[level], mg.ncomp[level]
+    basis = synth.gaussian_vectors(V, 16, nc, 71) / np.sqrt(2.0 * nc * np.prod(block))
+    mg.set_basis(level, basis)
+    b32 = basis.astype(np.complex64)
+    f = synth.coarse_source(V, nc, nrhs, 72, np.complex64)
+    yc = synth.coarse_source(mg.volume[level + 1], 32, nrhs, 73, np.complex64)
+    y = torch.empty((mg.volume[level + 1], 32, nrhs), dtype=torch.complex64, device="cuda")
+    fo = torch.empty((V, nc, nrhs), dtype=torch.complex64, device="cuda")
+    mg.restrict(level, y, dev(f))
+    assert rel(host(y), O.restrict(b32.astype(np.complex128), f, dims, block)) < 1e-6
+    mg.prolong(level, fo, dev(yc))
+    assert rel(host(fo), O.prolong(b32.astype(np.complex128), yc, dims, block)) < 1e-6
+    mg.restrict(level, y, dev(f), prec="bf16")
+    assert rel(host(y), O.restrict_lowprec(b32, f, dims, block)) < 2e-6
+    mg.prolong(level, fo, dev(yc), prec="bf16")
+    assert rel(host(fo), O.prolong_lowprec(b32, yc, dims, block)) < 2e-6
+
+
 def test_restrict_prolong_bf16_unsupported(gpu_lib):
     """n_v = 8 has no matrix-core intergrid path: a clear UNSUPPORTED error."""
     import torch
