@@ -92,14 +92,13 @@ FINE_SOURCES = ("fine.hip", "internal.h", "api.hip")
 # it only while the kernel name, sources and configurations still match.
 FINE_TRAFFIC = {
     "kernel": "fine_walk_kernel<2, 0, false>",
-    "sources": "2bd0a9649f6a2c6c",
-    "configs": {"6": [2, [4, 4, 4, 3], 224], "12": [2, [24, 8, 2, 3], 224], "24": [2, [24, 8, 2, 3], 132],
-                "48": [2, [24, 4, 4, 3], 132], "64": [2, [6, 6, 6, 12], 132]},
-    "bytes_per_launch": 5.250e9,
-    "note": "2.0 x FETCH_SIZE + 1.0 x WRITE_SIZE per dispatch (copy-calibrated), mean over Nrhs 6, 12, 24, 48, 64; "
+    "sources": "c170025c246ffe7b",
+    "configs": {"12": [2, [3, 3, 8, 6], 128], "24": [2, [6, 3, 2, 12], 132], "48": [2, [3, 3, 2, 24], 132],
+                "64": [2, [4, 2, 2, 12], 132]},
+    "bytes_per_launch": 4.692e9,
+    "note": "2.0 x FETCH_SIZE + 1.0 x WRITE_SIZE per dispatch (copy-calibrated), mean over Nrhs 12, 24, 48, 64; "
             "profiles/fine_kernel_hbm_counters_24x24x24x24.md",
 }
-
 
 
 def fine_sources_digest():
@@ -125,11 +124,20 @@ def coarse_flops(V, n):
 
 def fine_kernel_name(ctx, n):
     """Template instance of the FP32 fine kernel the tuned configuration of n uses."""
-    R, _, variant, _ = ctx.get_tuning(n)
+    R, tile, variant, _ = ctx.get_tuning(n)
     R = R or (2 if n % 2 == 0 else 1)
     occ = 4 if variant & 2 else 0
-    if variant & 128:  # the t-walk kernel
-        return f"fine_walk_kernel<{R}, {occ}, false>"  # false: D itself, not the fused residual
+    if variant & 128:  # a t-walk; false: D itself, not the fused residual
+        chunks = 1 << (variant >> 3 & 3)
+        bs, rows = tile[0] * tile[1] * tile[2], n // chunks // R
+        threads = -(-bs * rows // 64) * 64
+        faces = sum(bs // tile[m] for m in range(3) if DIMS[m] > tile[m])
+        words = next((i for i in range(1 if R == 2 else 3)
+                      if 18 * bs <= (3, 6, 9)[i] * threads and 9 * faces <= (2, 4, 4)[i] * threads), None)
+        thin = any(tile[m] == 1 < DIMS[m] for m in range(3))
+        if not occ and words is not None and threads <= 512 and not thin:  # its block in LDS
+            return f"fine_walk_kernel<{R}, {words}, false>"
+        return f"fine_walk_open_kernel<{R}, {occ}, false>"
     return f"fine_kernel<float, {R}, 0, true, true, {occ}, HIP_vector_type<float, 2u> >"
 
 

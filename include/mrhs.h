@@ -123,7 +123,8 @@ mrhs_status mrhs_get_clover(mrhs_ctx ctx, void* A, mrhs_prec prec, int32_t on_de
  * (M_ooee of Sec. 4).  in/out: device fields [V][12][nrhs] in prec
  * (MRHS_F32 or MRHS_F64); they must not overlap.  The launch configuration
  * is the one mrhs_tune chose for nrhs (FP32: mrhs_get_tuning; FP64:
- * mrhs_get_f64_walk), else a default; every configuration gives the same
+ * mrhs_get_f64_walk), else a default (FP32: the t-walk shape of the least
+ * estimated time; FP64: the tiled kernel); every configuration gives the same
  * bits.  MRHS_ERR_STATE before links and clover are set. */
 mrhs_status mrhs_dwc_apply(mrhs_ctx ctx, void* out, const void* in, int32_t nrhs, mrhs_prec prec);
 /* mrhs_hop_apply: out = H in (hopping term only, Sec. 4 D_hop). */
@@ -506,7 +507,8 @@ mrhs_status mrhs_mg_solve(mrhs_mg mg, void* x, const void* b, int32_t nrhs, cons
  * slices, one per XCD, and columns of the full time extent), two tile orders
  * (lexicographic, Morton), or the t-walk kernel (each thread walks a run of
  * time slices of one site of a spatial block, carrying its t-neighbours in
- * registers) with its block and run length, the right-hand sides split into 1, 2 or 4 chunks
+ * registers; a block that fits one workgroup is kept in LDS) with its block
+ * and run length, the right-hand sides split into 1, 2 or 4 chunks
  * swept one after the other, at most 1, 2 or 3 workgroups per CU or no limit,
  * two register budgets (the compiler's, and one that admits 4 wavefronts per
  * SIMD) and ordinary or non-temporal output stores -- on

@@ -110,7 +110,7 @@ mrhs_status fine_apply(mrhs_ctx ctx, int mode, void* out, const void* in, int32_
   hipError_t e;
   if (prec == MRHS_F32)
     e = launch_fine_f32(ctx->g, ctx->t_bc, mode, (float)ctx->kappa, ctx->U32.p, ctx->A32.p, in, out, nrhs,
-                        ctx->stream, &ctx->fine_cfg[nrhs]);
+                        ctx->stream, mode == 0 ? fine_config(ctx, nrhs) : &ctx->fine_cfg[nrhs]);
   else
     e = launch_fine_f64(ctx->g, ctx->t_bc, mode, ctx->kappa, ctx->U64.p, ctx->A64.p, in, out, nrhs, ctx->stream,
                         &ctx->f64_walk[nrhs]);
@@ -231,6 +231,12 @@ mrhs_status ensure_clover_inverse(mrhs_ctx ctx) {
 // either lexicographically (curve 0) or along a Morton curve in (x, y, z)
 // (curve 1), which keeps tiles that are neighbours in y and z close in time.
 // Sites inside a tile are lexicographic.
+const FineCfg* fine_config(mrhs_ctx ctx, int nrhs) {
+  if (ctx->fine_cfg[nrhs].R > 0) return &ctx->fine_cfg[nrhs];
+  std::call_once(ctx->fine_auto_once[nrhs], [&] { ctx->fine_auto[nrhs] = fine_default(ctx->g, nrhs); });
+  return &ctx->fine_auto[nrhs];
+}
+
 const int* fine_order_table(mrhs_ctx ctx, const int T[4], int curve) {
   std::array<int, 5> key{T[0], T[1], T[2], T[3], curve};
   for (auto& o : ctx->orders)

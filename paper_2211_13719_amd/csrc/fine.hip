@@ -20,6 +20,7 @@
 // gamma_4 = [[0, 1], [1, 0]].  Writing psi = (u0, u1, l0, l1) in spin, the
 // projection (1 -+ gamma_mu) psi has upper half h = (h0, h1) and lower half a
 // fixed multiple of h, listed per direction in project()/reconstruct().
+#include <algorithm>
 #include <type_traits>
 
 #include "internal.h"
@@ -770,7 +771,7 @@ __device__ __forceinline__ void walk_body(const Geom& g, int nrhs, T kappa, cons
 }
 
 template <int R, int OCC, bool RES = false>
-__global__ __launch_bounds__(256, (OCC > 0 ? OCC : 1)) void fine_walk_kernel(Geom g, int nrhs, float kappa,
+__global__ __launch_bounds__(256, (OCC > 0 ? OCC : 1)) void fine_walk_open_kernel(Geom g, int nrhs, float kappa,
                                                                            const cplx<float>* __restrict__ U,
                                                                            const float* __restrict__ A,
                                                                            const cplx<float>* __restrict__ in,
@@ -782,7 +783,7 @@ __global__ __launch_bounds__(256, (OCC > 0 ? OCC : 1)) void fine_walk_kernel(Geo
 
 // The FP64 operator of the outer solver's residuals, one RHS per thread.
 template <int OCC>
-__global__ __launch_bounds__(256, (OCC > 0 ? OCC : 1)) void fine_walk_f64_kernel(Geom g, int nrhs, double kappa,
+__global__ __launch_bounds__(256, (OCC > 0 ? OCC : 1)) void fine_walk_open_f64_kernel(Geom g, int nrhs, double kappa,
                                                             const cplx<double>* __restrict__ U,
                                                             const double* __restrict__ A,
                                                             const cplx<double>* __restrict__ in,
@@ -812,12 +813,455 @@ bool walk_shape(const Geom& g, const int T[4], int nrhs, int R, int chunks, Walk
   return w.per * 8 <= 0x7fffffffL;
 }
 
+// ---- the t-walk with its block in LDS ----
+// The walk above leaves the re-reads of a slice's spatial neighbours to the
+// caches; the threads of a block drift apart and most of them miss.  And each
+// vector memory instruction of a wavefront takes its cycles in the CU's
+// address pipeline whether its lanes ask for 16 bytes or share one word, so
+// the loads of a site's links, the same for all its right-hand sides, cost as
+// much there as spinor rows.  Here one workgroup owns a whole block and one
+// chunk of right-hand sides.  Per slice it keeps in LDS the block's spinor
+// rows, each written once by its own thread (13 vectors apart, an odd stride:
+// no bank conflicts), and the links of the block and of its backward faces,
+// fetched together as flat 16-byte words and shared by all.  Rows from
+// outside the block are read straight from memory where they are needed; the
+// next slice's own rows and links are in flight under the last hops and
+// change places with this slice's between two barriers.  Consecutive
+// workgroups walk a 2 x 2 x 2 group of blocks, so the faces they share are
+// read at about the same time.  Order and arithmetic of the hops are those of
+// the other kernels, so the results are bit-identical.
+//
+// Measured, the best shape of the walk above against the best of this one: 24^4
+// FP32, Nrhs 2 / 4 / 6 / 12 / 24 / 48 / 64: 148 / 216 / 288 / 424 / 690 / 1246 /
+// 1595 against 100 / 147 / 207 / 320 / 558 / 1019 / 1343 us; 16^3 x 32, Nrhs 12:
+// 185 against 109 us; FP64 on 24^4, Nrhs 4 / 12: 353 / 891 against 288 / 767 us.
+// At Nrhs 12 it reads 1.18 instead of 1.85 GB from outside the L2s.  It is
+// bound by issue and latency together: 256 registers leave two wavefronts per
+// SIMD to hide the halo rows' latency (an earlier fetch of them needs more
+// registers and gained nothing).  At one right-hand side the links are most of
+// the bytes and are not shared: blocks beyond 32 sites keep the walk above,
+// 78 against 82 us on 24^4.
+struct StagedWalk {
+  int B[3];       // spatial block extents
+  int nb[3];      // blocks along x, y, z
+  int sup[3];     // blocks along x, y, z that are walked one after the other
+  int Ts;         // time slices per workgroup
+  int nc;         // right-hand sides per chunk
+  int bs;         // sites per block
+  int nchunk;     // chunks of right-hand sides
+  int nblk;       // blocks per time slice
+  int threads;    // per workgroup
+  unsigned lds;   // bytes per workgroup
+  long total_wg;  // workgroups of the whole launch
+  long per;       // workgroups per XCD
+};
+
+template <typename T, int R>
+using row_vec __attribute__((ext_vector_type(2 * R))) = T;
+template <typename T, int R>
+__device__ __forceinline__ void ldo(const cplx<T>* __restrict__ base, unsigned off, cplx<T> (&v)[R]) {
+  const row_vec<T, R> w = *reinterpret_cast<const row_vec<T, R>*>(reinterpret_cast<const char*>(base) + off);
+#pragma unroll
+  for (int j = 0; j < R; ++j) v[j] = mk<T>(w[2 * j], w[2 * j + 1]);
+}
+template <typename T, int R>
+__device__ __forceinline__ void lget(const row_vec<T, R>* p, cplx<T> (&v)[R]) {
+  const row_vec<T, R> w = *p;
+#pragma unroll
+  for (int j = 0; j < R; ++j) v[j] = mk<T>(w[2 * j], w[2 * j + 1]);
+}
+template <typename T, int R>
+__device__ __forceinline__ void lput(row_vec<T, R>* p, const cplx<T> (&v)[R]) {
+  row_vec<T, R> w;
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    w[2 * j] = v[j].x;
+    w[2 * j + 1] = v[j].y;
+  }
+  *p = w;
+}
+
+
+// Link words (16 bytes) and halo-link entries that a thread stages, at most;
+// FP32 blocks of LINKS 0 have six or more threads per site and chunk, of 1
+// three or more, of 2 two or more.
+constexpr int kStagedWords[3] = {3, 6, 9}, kStagedHalo[3] = {2, 4, 4};
+constexpr int kStagedThreads = 512;
+
+template <typename T, int R, int LINKS, bool RES>
+__device__ __forceinline__ void staged_walk(const Geom& g, int nrhs, T kappa, const cplx<T>* __restrict__ U,
+                                            const T* __restrict__ A, const cplx<T>* __restrict__ in,
+                                            cplx<T>* __restrict__ out, const StagedWalk& w, int nt_out,
+                                            const cplx<T>* __restrict__ bres) {
+  constexpr int UPS = 36 * (int)sizeof(cplx<T>) / 16;  // 16-byte words of one site's links
+  constexpr int NL = kStagedWords[LINKS], NH = kStagedHalo[LINKS];
+  extern __shared__ __attribute__((aligned(16))) char walk_lds[];
+  const int th = (int)blockDim.x;
+  row_vec<T, R>* own = reinterpret_cast<row_vec<T, R>*>(walk_lds);     // [thread][13], 12 used
+  f32x4_nt* lnk = reinterpret_cast<f32x4_nt*>(own + 13 * th);          // [site][UPS]
+  cplx<T>* hlk = reinterpret_cast<cplx<T>*>(lnk + w.bs * UPS);  // backward links from outside the block, ten elements each
+  const int hw = blockIdx.x;
+  const long wgi = (long)(hw & 7) * w.per + (hw >> 3);
+  if (wgi >= w.total_wg) return;
+  const int chunk = (int)(wgi % w.nchunk);
+  const int ub = (int)(wgi / w.nchunk);
+  const int blk = ub % w.nblk;
+  const int seg = ub / w.nblk;
+  int bx, by, bz;
+  {
+    const int ss = w.sup[0] * w.sup[1] * w.sup[2];
+    const int sup = blk / ss;
+    int r = blk - sup * ss;
+    const int n0 = w.nb[0] / w.sup[0], n1 = w.nb[1] / w.sup[1];
+    bx = (sup % n0) * w.sup[0] + r % w.sup[0];
+    r /= w.sup[0];
+    by = ((sup / n0) % n1) * w.sup[1] + r % w.sup[1];
+    bz = (sup / (n0 * n1)) * w.sup[2] + r / w.sup[1];
+  }
+  const int x0 = bx * w.B[0], y0 = by * w.B[1], z0 = bz * w.B[2];
+  const int tid = threadIdx.x;
+  const int C = w.nc / R;  // threads per site
+  const int nact = w.bs * C;
+  const bool valid = tid < nact;
+  const int tv = valid ? tid : nact - 1;
+  const int sb = tv / C;
+  const int k = tv - sb * C;
+  const int lx = sb % w.B[0], ly = (sb / w.B[0]) % w.B[1], lz = sb / (w.B[0] * w.B[1]);
+  const int x = x0 + lx, y = y0 + ly, z = z0 + lz;
+  const int xs = x + g.stride[1] * y + g.stride[2] * z;
+  const int Vs = g.stride[3];
+  const int rs = 12 * nrhs;
+  const unsigned rb = (unsigned)rs * sizeof(cplx<T>);
+  const int k0 = chunk * w.nc;
+  const unsigned voff = (unsigned)xs * rb + (unsigned)k * (unsigned)(R * sizeof(cplx<T>));
+  // halo of this thread: at most one per dimension (blocks are at least two
+  // wide, or span the lattice and wrap into themselves)
+  const bool hx = w.nb[0] > 1 && (lx == 0 || lx == w.B[0] - 1);
+  const bool hy = w.nb[1] > 1 && (ly == 0 || ly == w.B[1] - 1);
+  const bool hz = w.nb[2] > 1 && (lz == 0 || lz == w.B[2] - 1);
+  const int dx = lx == 0 ? (x > 0 ? -1 : g.L[0] - 1) : (x + 1 < g.L[0] ? 1 : 1 - g.L[0]);
+  const int dy = (ly == 0 ? (y > 0 ? -1 : g.L[1] - 1) : (y + 1 < g.L[1] ? 1 : 1 - g.L[1])) * g.stride[1];
+  const int dz = (lz == 0 ? (z > 0 ? -1 : g.L[2] - 1) : (z + 1 < g.L[2] ? 1 : 1 - g.L[2])) * g.stride[2];
+  const unsigned voffx = voff + (unsigned)(dx * (int)rb);
+  const unsigned voffy = voff + (unsigned)dy * rb;
+  const unsigned voffz = voff + (unsigned)dz * rb;
+  // in-block neighbours
+  const int sx = C, sy = sx * w.B[0], sz = sy * w.B[1];
+  const bool ixf = !hx || lx == 0, ixb = !hx || lx != 0;
+  const bool iyf = !hy || ly == 0, iyb = !hy || ly != 0;
+  const bool izf = !hz || lz == 0, izb = !hz || lz != 0;
+  const int pxf = tv + (lx + 1 < w.B[0] ? sx : sx * (1 - w.B[0])), pxb = tv + (lx > 0 ? -sx : sx * (w.B[0] - 1));
+  const int pyf = tv + (ly + 1 < w.B[1] ? sy : sy * (1 - w.B[1])), pyb = tv + (ly > 0 ? -sy : sy * (w.B[1] - 1));
+  const int pzf = tv + (lz + 1 < w.B[2] ? sz : sz * (1 - w.B[2])), pzb = tv + (lz > 0 ? -sz : sz * (w.B[2] - 1));
+  const cplx<T>* lk = reinterpret_cast<const cplx<T>*>(lnk);
+  const int fX = w.nb[0] > 1 ? w.B[1] * w.B[2] : 0, fY = w.nb[1] > 1 ? w.B[0] * w.B[2] : 0,
+            fZ = w.nb[2] > 1 ? w.B[0] * w.B[1] : 0;
+  const cplx<T>* lxb = ixb ? lk + (sb + (lx > 0 ? -1 : w.B[0] - 1)) * 36 : hlk + (lz * w.B[1] + ly) * 10;
+  const cplx<T>* lyb = iyb ? lk + (sb + (ly > 0 ? -1 : w.B[1] - 1) * w.B[0]) * 36 + 9
+                           : hlk + (fX + lz * w.B[0] + lx) * 10 + 1;
+  const cplx<T>* lzb = izb ? lk + (sb + (lz > 0 ? -1 : w.B[2] - 1) * w.B[0] * w.B[1]) * 36 + 18
+                           : hlk + (fX + fY + ly * w.B[0] + lx) * 10;
+  // this thread's share of the block's links and clover blocks: 16-byte words
+  // p = tid + j TH of the bs UPS words, and entries of the backward halo links
+  unsigned lo[NL], ho[NH];
+#pragma unroll
+  for (int j = 0; j < NL; ++j) {
+    int p = tid + j * th;
+    if (p >= w.bs * UPS) p = w.bs * UPS - 1;
+    const int s = p / UPS;
+    const int cx = x0 + s % w.B[0], cy = y0 + (s / w.B[0]) % w.B[1], cz = z0 + s / (w.B[0] * w.B[1]);
+    lo[j] = ((unsigned)(cx + g.stride[1] * cy + g.stride[2] * cz) * UPS + (unsigned)(p - s * UPS)) * 16u;
+  }
+  const int nhl = (fX + fY + fZ) * 9;
+  // where halo entry p goes: ten per link, those of the y faces eight bytes
+  // on, so that an odd link starts off a 16-byte boundary as it does in U
+  const auto hslot = [&](int p) {
+    const int q = p / 9;
+    return p + q + (q >= fX && q < fX + fY);
+  };
+#pragma unroll
+  for (int j = 0; j < NH; ++j) {
+    int p = tid + j * th;
+    if (p >= nhl) p = nhl > 0 ? nhl - 1 : 0;
+    int q = p / 9;
+    const int e = p - 9 * q;
+    int cx = x0, cy = y0, cz = z0, mu;
+    if (q < fX) {
+      mu = 0;
+      cx = x0 > 0 ? x0 - 1 : g.L[0] - 1;
+      cy += q % w.B[1];
+      cz += q / w.B[1];
+    } else if (q < fX + fY) {
+      q -= fX;
+      mu = 1;
+      cy = y0 > 0 ? y0 - 1 : g.L[1] - 1;
+      cx += q % w.B[0];
+      cz += q / w.B[0];
+    } else {
+      q -= fX + fY;
+      mu = 2;
+      cz = z0 > 0 ? z0 - 1 : g.L[2] - 1;
+      cx += q % w.B[0];
+      cy += q / w.B[0];
+    }
+    ho[j] = nhl > 0 ? (unsigned)((cx + g.stride[1] * cy + g.stride[2] * cz) * 36 + mu * 9 + e) * (unsigned)sizeof(cplx<T>)
+                    : 0u;
+  }
+
+  const int t0 = seg * w.Ts;
+  const size_t fs = (size_t)Vs * rs;  // elements of one time slice of a field
+  const size_t ls = (size_t)Vs * 36;  // of the links
+  const cplx<T>* fin = in + k0;
+  cplx<T> bwd[2][3][R];
+#define WALK_LOAD(dst, base, off)                                                                   \
+  {                                                                                                 \
+    const cplx<T>* b_ = (base);                                                                     \
+    _Pragma("unroll") for (int c = 0; c < 12; ++c) ldo<T, R>(b_ + c * nrhs, off, dst[c / 3][c % 3]); \
+  }
+  {
+    cplx<T> p[4][3][R], h[2][3][R], uu[3][3];
+    const int tm = (t0 == 0 ? g.L[3] : t0) - 1;
+    const cplx<T>* f0 = fin + fs * t0;
+    WALK_LOAD(p, fin + fs * tm, voff)
+    load_link<T, 3>(U + ls * tm + (size_t)xs * 36 + 27, uu);
+    f32x4_nt lw[NL];
+    cplx<T> hv[NH];
+    const char* ub_ = reinterpret_cast<const char*>(U + ls * t0);
+#pragma unroll
+    for (int j = 0; j < NL; ++j)
+      if (j * th < w.bs * UPS) lw[j] = *reinterpret_cast<const f32x4_nt*>(ub_ + lo[j]);
+#pragma unroll
+    for (int j = 0; j < NH; ++j)
+      if (j * th < nhl) hv[j] = *reinterpret_cast<const cplx<T>*>(ub_ + ho[j]);
+    project<T, R, 3, -1>(p, h);
+    transport_dag<R, T>(uu, h, bwd);
+    WALK_LOAD(p, f0, voff)
+    if (valid) {
+#pragma unroll
+      for (int c = 0; c < 12; ++c) lput<T, R>(own + 13 * tv + c, p[c / 3][c % 3]);
+    }
+#pragma unroll
+    for (int j = 0; j < NL; ++j)
+      if (tid + j * th < w.bs * UPS) lnk[tid + j * th] = lw[j];
+#pragma unroll
+    for (int j = 0; j < NH; ++j)
+      if (tid + j * th < nhl) hlk[hslot(tid + j * th)] = hv[j];
+  }
+  __syncthreads();
+  for (int i = 0; i < w.Ts; ++i) {
+    const int t = t0 + i;
+    const bool more = i + 1 < w.Ts;
+    cplx<T> nxt[4][3][R];
+    const cplx<T>* fn = fin + fs * (t + 1 == g.L[3] ? 0 : t + 1);
+    const cplx<T>* ft = fin + fs * t;
+    cplx<T> acc[4][3][R];
+#pragma unroll
+    for (int c = 0; c < 12; ++c)
+#pragma unroll
+      for (int j = 0; j < R; ++j) acc[c / 3][c % 3][j] = mk<T>(0, 0);
+#define WALK_HOP(MU, S, inb, pn, hoff, link)                                                        \
+  {                                                                                                 \
+    cplx<T> p[4][3][R], h[2][3][R], wv[2][3][R], uu[3][3];                                          \
+    if (inb) {                                                                                      \
+      _Pragma("unroll") for (int c = 0; c < 12; ++c) lget<T, R>(own + 13 * pn + c, p[c / 3][c % 3]);          \
+    } else {                                                                                        \
+      WALK_LOAD(p, ft, hoff)                                                                        \
+    }                                                                                               \
+    load_link<T, MU>(link, uu);                                                                     \
+    project<T, R, MU, S>(p, h);                                                                     \
+    if constexpr (S > 0)                                                                            \
+      transport<R, T>(uu, h, wv);                                                                   \
+    else                                                                                            \
+      transport_dag<R, T>(uu, h, wv);                                                               \
+    reconstruct<T, R, MU, S>(acc, wv);                                                              \
+    pin<T, R>(acc);                                                                                 \
+    __builtin_amdgcn_sched_barrier(0);                                                              \
+  }
+    const cplx<T>* lf = lk + sb * 36;
+    WALK_HOP(0, +1, ixf, pxf, voffx, lf)
+    WALK_HOP(0, -1, ixb, pxb, voffx, lxb)
+    WALK_HOP(1, +1, iyf, pyf, voffy, lf + 9)
+    WALK_HOP(1, -1, iyb, pyb, voffy, lyb)
+    WALK_HOP(2, +1, izf, pzf, voffz, lf + 18)
+    WALK_LOAD(nxt, fn, voff)
+    WALK_HOP(2, -1, izb, pzb, voffz, lzb)
+#undef WALK_HOP
+    f32x4_nt lw[NL];
+    cplx<T> hv[NH];
+    if (more) {
+      const char* ub_ = reinterpret_cast<const char*>(U + ls * (t + 1));
+#pragma unroll
+      for (int j = 0; j < NL; ++j)
+      if (j * th < w.bs * UPS) lw[j] = *reinterpret_cast<const f32x4_nt*>(ub_ + lo[j]);
+#pragma unroll
+      for (int j = 0; j < NH; ++j)
+        if (j * th < nhl) hv[j] = *reinterpret_cast<const cplx<T>*>(ub_ + ho[j]);
+    }
+    cplx<T> uu[3][3];
+    load_link<T, 3>(lf + 27, uu);
+    {
+      cplx<T> h[2][3][R], wv[2][3][R];
+      project<T, R, 3, +1>(nxt, h);
+      transport<R, T>(uu, h, wv);
+      reconstruct<T, R, 3, +1>(acc, wv);
+      pin<T, R>(acc);
+    }
+    reconstruct<T, R, 3, -1>(acc, bwd);
+    pin<T, R>(acc);
+    __builtin_amdgcn_sched_barrier(0);
+    cplx<T> self[4][3][R];
+#pragma unroll
+    for (int c = 0; c < 12; ++c) lget<T, R>(own + 13 * tv + c, self[c / 3][c % 3]);
+    {
+      cplx<T> h[2][3][R];
+      project<T, R, 3, -1>(self, h);
+      transport_dag<R, T>(uu, h, bwd);
+    }
+    cplx<T>* ob = out + k0 + fs * t;
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int chi = 0; chi < 2; ++chi) {
+      __builtin_amdgcn_sched_barrier(0);
+      cplx<T> xin[6][R], yout[6][R];
+#pragma unroll
+      for (int q = 0; q < 6; ++q)
+#pragma unroll
+        for (int j = 0; j < R; ++j) xin[q][j] = self[(6 * chi + q) / 3][(6 * chi + q) % 3][j];
+      clover_block<T, R>(A + ((size_t)Vs * t + xs) * 72 + chi * 36, xin, yout);
+#pragma unroll
+      for (int q = 0; q < 6; ++q) {
+        const int sp = 2 * chi + q / 3, c = q % 3;
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+          yout[q][j].x = fma(-kappa, acc[sp][c][j].x, yout[q][j].x);
+          yout[q][j].y = fma(-kappa, acc[sp][c][j].y, yout[q][j].y);
+        }
+        if constexpr (RES) {
+          cplx<T> bv[R];
+          ldo<T, R>(bres + k0 + fs * t + (6 * chi + q) * nrhs, voff, bv);
+#pragma unroll
+          for (int j = 0; j < R; ++j) yout[q][j] = sub<T>(bv[j], yout[q][j]);
+        }
+        if (valid)
+          store_r<T, R>(reinterpret_cast<cplx<T>*>(reinterpret_cast<char*>(ob + (6 * chi + q) * nrhs) + voff), yout[q],
+                        nt_out);
+      }
+    }
+    if (!more) break;
+    __syncthreads();
+    if (valid) {
+#pragma unroll
+      for (int c = 0; c < 12; ++c) lput<T, R>(own + 13 * tv + c, nxt[c / 3][c % 3]);
+    }
+#pragma unroll
+    for (int j = 0; j < NL; ++j)
+      if (tid + j * th < w.bs * UPS) lnk[tid + j * th] = lw[j];
+#pragma unroll
+    for (int j = 0; j < NH; ++j)
+      if (tid + j * th < nhl) hlk[hslot(tid + j * th)] = hv[j];
+    __syncthreads();
+  }
+#undef WALK_LOAD
+}
+
+// FP32: 256 registers (two wavefronts per SIMD), FP64 up to 512 for
+// workgroups of at most 256 threads.
+template <int R, int LINKS, bool RES>
+__global__ __launch_bounds__(kStagedThreads, 2) void fine_walk_kernel(Geom g, int nrhs, float kappa,
+                                                                      const cplx<float>* __restrict__ U,
+                                                                      const float* __restrict__ A,
+                                                                      const cplx<float>* __restrict__ in,
+                                                                      cplx<float>* __restrict__ out, StagedWalk w,
+                                                                      int nt_out, const cplx<float>* __restrict__ bres) {
+  staged_walk<float, R, LINKS, RES>(g, nrhs, kappa, U, A, in, out, w, nt_out, bres);
+}
+
+template <int LINKS>
+__global__ __launch_bounds__(256, 1) void fine_walk_f64_kernel(Geom g, int nrhs, double kappa,
+                                                               const cplx<double>* __restrict__ U,
+                                                               const double* __restrict__ A,
+                                                               const cplx<double>* __restrict__ in,
+                                                               cplx<double>* __restrict__ out, StagedWalk w,
+                                                               int nt_out) {
+  staged_walk<double, 1, LINKS, false>(g, nrhs, kappa, U, A, in, out, w, nt_out, nullptr);
+}
+
+// Shape of a staged walk for tile T = (Bx, By, Bz, Ts); links = which of the
+// two instances it takes.  False where it does not fit: the tile does not
+// divide the lattice; a block one site wide that does not span the lattice
+// (its sites would have two neighbours outside in one dimension); more
+// threads, link words or LDS than one workgroup has; a time slice beyond the
+// 32-bit byte offsets.
+bool staged_shape(const Geom& g, const int T[4], int nrhs, int R, int chunks, int real_bytes, int max_threads,
+                  StagedWalk& w, int& links) {
+  for (int m = 0; m < 4; ++m)
+    if (T[m] < 1 || g.L[m] % T[m]) return false;
+  if (chunks < 1 || nrhs % chunks || (nrhs / chunks) % R) return false;
+  w.nc = nrhs / chunks;
+  w.nchunk = chunks;
+  w.Ts = T[3];
+  const long bs = (long)T[0] * T[1] * T[2];
+  if (bs * (w.nc / R) > max_threads) return false;
+  w.bs = (int)bs;
+  int face[3];
+  for (int m = 0; m < 3; ++m) {
+    w.B[m] = T[m];
+    w.nb[m] = g.L[m] / T[m];
+    if (w.nb[m] > 1 && T[m] < 2) return false;
+    w.sup[m] = w.nb[m] % 2 == 0 ? 2 : 1;
+    face[m] = w.nb[m] > 1 ? w.bs / T[m] : 0;
+  }
+  w.nblk = w.nb[0] * w.nb[1] * w.nb[2];
+  w.threads = (w.bs * (w.nc / R) + 63) / 64 * 64;
+  const int words = w.bs * 36 * 2 * real_bytes / 16, halo = face[0] + face[1] + face[2];
+  const int variants = R > 1 ? 1 : 3;
+  for (links = 0; links < variants; ++links)
+    if (words <= kStagedWords[links] * w.threads && halo * 9 <= kStagedHalo[links] * w.threads) break;
+  if (links == variants) return false;
+  const long lds = (long)w.threads * 13 * 2 * R * real_bytes + (long)words * 16 + (long)halo * 20 * real_bytes;
+  if (lds > 160 * 1024) return false;
+  w.lds = (unsigned)lds;
+  const long slice = (long)g.stride[3] * 12 * nrhs * 2 * real_bytes;
+  if (slice >= (1L << 31) || (long)g.stride[3] * 36 * 2 * real_bytes >= (1L << 31)) return false;
+  w.total_wg = (long)chunks * w.nblk * (g.L[3] / T[3]);
+  w.per = (w.total_wg + 7) / 8;
+  return w.per * 8 <= 0x7fffffffL;
+}
+
+// FP64: the fewest chunks of right-hand sides that fit the workgroup.
+bool staged_shape_f64(const Geom& g, const int T[4], int nrhs, StagedWalk& w, int& links) {
+  for (int c = 1; c <= nrhs; ++c)
+    if (nrhs % c == 0 && (long)T[0] * T[1] * T[2] * (nrhs / c) <= 256)
+      return staged_shape(g, T, nrhs, 1, c, 8, 256, w, links);
+  return false;
+}
+
+template <int R, int LINKS, bool RES>
+hipError_t launch_staged_k(const Geom& g, const StagedWalk& w, const FineCfg& c, float kappa, const void* U,
+                           const void* A, const void* in, void* out, int nrhs, hipStream_t s, const void* bres) {
+  hipLaunchKernelGGL((fine_walk_kernel<R, LINKS, RES>), dim3((unsigned)(w.per * 8)), dim3((unsigned)w.threads),
+                     c.lds > w.lds ? c.lds : w.lds, s, g, nrhs, kappa, reinterpret_cast<const cplx<float>*>(U),
+                     reinterpret_cast<const float*>(A), reinterpret_cast<const cplx<float>*>(in),
+                     reinterpret_cast<cplx<float>*>(out), w, c.nt, reinterpret_cast<const cplx<float>*>(bres));
+  return hipGetLastError();
+}
+
+template <int R, bool RES>
+hipError_t launch_staged(const Geom& g, const StagedWalk& w, int links, const FineCfg& c, float kappa, const void* U,
+                         const void* A, const void* in, void* out, int nrhs, hipStream_t s, const void* bres) {
+  if constexpr (R == 1) {
+    if (links == 2) return launch_staged_k<R, 2, RES>(g, w, c, kappa, U, A, in, out, nrhs, s, bres);
+    if (links == 1) return launch_staged_k<R, 1, RES>(g, w, c, kappa, U, A, in, out, nrhs, s, bres);
+  }
+  return launch_staged_k<R, 0, RES>(g, w, c, kappa, U, A, in, out, nrhs, s, bres);
+}
+
 template <int R, int OCC, bool RES>
 hipError_t launch_walk_r(const Geom& g, const FineCfg& c, float kappa, const void* U, const void* A, const void* in,
                          void* out, int nrhs, hipStream_t s, const void* bres) {
   WalkShape w;
   if (!walk_shape(g, c.T, nrhs, R, c.chunks, w)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((fine_walk_kernel<R, OCC, RES>), dim3((unsigned)(w.per * 8)), dim3(256), c.lds, s, g, nrhs,
+  hipLaunchKernelGGL((fine_walk_open_kernel<R, OCC, RES>), dim3((unsigned)(w.per * 8)), dim3(256), c.lds, s, g, nrhs,
                      kappa, reinterpret_cast<const cplx<float>*>(U), reinterpret_cast<const float*>(A),
                      reinterpret_cast<const cplx<float>*>(in), reinterpret_cast<cplx<float>*>(out), w, c.nt,
                      reinterpret_cast<const cplx<float>*>(bres));
@@ -828,6 +1272,12 @@ hipError_t launch_walk_r(const Geom& g, const FineCfg& c, float kappa, const voi
 template <bool RES>
 hipError_t launch_walk_res(const Geom& g, const FineCfg& c, float kappa, const void* U, const void* A, const void* in,
                            void* out, int nrhs, hipStream_t s, const void* bres) {
+  StagedWalk w;
+  int links = 0;
+  if (c.occ == 0 && staged_shape(g, c.T, nrhs, c.R, c.chunks, 4, kStagedThreads, w, links)) {
+    if (c.R == 2) return launch_staged<2, RES>(g, w, links, c, kappa, U, A, in, out, nrhs, s, bres);
+    if (c.R == 1) return launch_staged<1, RES>(g, w, links, c, kappa, U, A, in, out, nrhs, s, bres);
+  }
   if (c.occ == 4) {
     if (c.R == 2) return launch_walk_r<2, 4, RES>(g, c, kappa, U, A, in, out, nrhs, s, bres);
     if (c.R == 1) return launch_walk_r<1, 4, RES>(g, c, kappa, U, A, in, out, nrhs, s, bres);
@@ -1458,6 +1908,74 @@ bool launch_fine_residual_f32(const Geom& g, float kappa, const void* U, const v
   return true;
 }
 
+double staged_walk_cost(const Geom& g, const int tile[4], int nrhs, int R, int chunks, bool f64) {
+  StagedWalk w;
+  int links = 0;
+  if (f64 ? !staged_shape_f64(g, tile, nrhs, w, links)
+          : !staged_shape(g, tile, nrhs, R, chunks, 4, kStagedThreads, w, links))
+    return -1.0;
+  const int waves = w.threads / 64;
+  const long res = std::max<long>(1, std::min({160 * 1024L / w.lds, (long)(f64 ? 4 : 8) / waves, (w.total_wg + 255) / 256}));
+  const double rounds = (double)((w.total_wg + 256 * res - 1) / (256 * res)), simd = res * waves / 4.0;
+  double halo = 0.0;  // rows from outside the block per row of it
+  for (int m = 0; m < 3; ++m)
+    if (w.nb[m] > 1) halo += 2.0 / w.B[m];
+  return rounds * (simd + (f64 ? 2.0 : 0.75)) * (w.Ts + 1.0) * (1.0 + 0.05 * halo) * (1.0 + 2.0 / w.nc) *
+         (R == 2 ? 1.0 : 0.65);
+}
+
+// Every staged walk of the lattice, as f(tile, R, chunks, cost).
+template <typename F>
+void each_staged_walk(const Geom& g, int nrhs, bool f64, F f) {
+  for (int R = 1; R <= (f64 ? 1 : 2); ++R)
+    for (int chunks = 1; chunks <= (f64 ? 1 : 4); chunks *= 2) {
+      if (nrhs % chunks || (nrhs / chunks) % R) continue;
+      const int smax = (f64 ? 256 : kStagedThreads) / (f64 ? 1 : nrhs / chunks / R);  // sites of a block
+      for (int bx = 1; bx <= g.L[0] && bx <= smax; ++bx)
+        for (int by = 1; g.L[0] % bx == 0 && by <= g.L[1] && bx * by <= smax; ++by)
+          for (int bz = 1; g.L[1] % by == 0 && bz <= g.L[2] && bx * by * bz <= smax; ++bz)
+            for (int ts = 1; g.L[2] % bz == 0 && ts <= g.L[3]; ++ts) {
+              if (g.L[3] % ts) continue;
+              const int tile[4] = {bx, by, bz, ts};
+              const double cost = staged_walk_cost(g, tile, nrhs, R, chunks, f64);
+              if (cost >= 0.0) f(tile, R, chunks, cost);
+            }
+    }
+}
+
+std::vector<FineCfg> staged_walks(const Geom& g, int nrhs, bool f64, size_t count) {
+  std::vector<std::pair<double, FineCfg>> all;
+  each_staged_walk(g, nrhs, f64, [&](const int* tile, int R, int chunks, double cost) {
+    FineCfg c;
+    c.walk = 1;
+    c.R = R;
+    c.chunks = chunks;
+    for (int m = 0; m < 4; ++m) c.T[m] = tile[m];
+    all.emplace_back(cost, c);
+  });
+  std::stable_sort(all.begin(), all.end(), [](const auto& a, const auto& b) { return a.first < b.first; });
+  std::vector<FineCfg> out;
+  for (size_t i = 0; i < all.size() && i < count; ++i) out.push_back(all[i].second);
+  return out;
+}
+
+FineCfg fine_default(const Geom& g, int nrhs) {
+  FineCfg best;
+  double cost = 0.0;
+  each_staged_walk(g, nrhs, false, [&](const int* tile, int R, int chunks, double c) {
+    if (best.R && c >= cost) return;
+    cost = c;
+    best.walk = 1;
+    best.R = R;
+    best.chunks = chunks;
+    for (int m = 0; m < 4; ++m) best.T[m] = tile[m];
+  });
+  // chunks of 16 and more write whole 128-byte lines, which need not stay in
+  // the cache; non-temporal stores of less than a line cost up to a tenth
+  best.nt = best.R && nrhs / best.chunks >= 16;
+  return best;
+}
+
 bool f64_walk_fits(const Geom& g, const int tile[4], int nrhs) {
   WalkShape w;
   return walk_shape(g, tile, nrhs, 1, 1, w);
@@ -1467,9 +1985,18 @@ hipError_t launch_fine_f64(const Geom& g, int t_bc, int mode, double kappa, cons
                            const void* in, void* out, int nrhs, hipStream_t s, const F64Walk* fw) {
   if (mode == 0 && fw && fw->on) {
     const int tile[4] = {fw->B[0], fw->B[1], fw->B[2], fw->Ts};
+    StagedWalk sw;
+    int links = 0;
+    if (fw->occ == 0 && staged_shape_f64(g, tile, nrhs, sw, links)) {
+      auto k = links == 2 ? fine_walk_f64_kernel<2> : links == 1 ? fine_walk_f64_kernel<1> : fine_walk_f64_kernel<0>;
+      hipLaunchKernelGGL(k, dim3((unsigned)(sw.per * 8)), dim3((unsigned)sw.threads), sw.lds, s, g, nrhs, kappa,
+                         static_cast<const cplx<double>*>(U), static_cast<const double*>(A),
+                         static_cast<const cplx<double>*>(in), static_cast<cplx<double>*>(out), sw, fw->nt);
+      return hipGetLastError();
+    }
     WalkShape w;
     if (!walk_shape(g, tile, nrhs, 1, 1, w)) return hipErrorInvalidValue;
-    auto k = fw->occ == 2 ? fine_walk_f64_kernel<2> : fine_walk_f64_kernel<0>;
+    auto k = fw->occ == 2 ? fine_walk_open_f64_kernel<2> : fine_walk_open_f64_kernel<0>;
     hipLaunchKernelGGL(k, dim3((unsigned)(w.per * 8)), dim3(256), 0, s, g, nrhs, kappa,
                        static_cast<const cplx<double>*>(U), static_cast<const double*>(A),
                        static_cast<const cplx<double>*>(in), static_cast<cplx<double>*>(out), w, fw->nt);

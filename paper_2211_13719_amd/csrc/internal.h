@@ -7,6 +7,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <array>
+#include <mutex>
 #include <string>
 #include <utility>
 #include <vector>
@@ -139,6 +140,9 @@ struct mrhs_ctx_s {
 
   // autotuned launch configurations of the FP32 fine kernel, by nrhs
   mrhs::FineCfg fine_cfg[MRHS_MAX_NRHS + 1];
+  // and of the untuned one, worked out on first use of each nrhs
+  mrhs::FineCfg fine_auto[MRHS_MAX_NRHS + 1];
+  std::once_flag fine_auto_once[MRHS_MAX_NRHS + 1];
   mrhs::EoWalk eo_walk[MRHS_MAX_NRHS + 1];
   mrhs::F64Walk f64_walk[MRHS_MAX_NRHS + 1];
 
@@ -156,6 +160,9 @@ struct mrhs_ctx_s {
 };
 
 namespace mrhs {
+
+// The launch configuration of the FP32 operator A - kappa H at nrhs.
+const FineCfg* fine_config(mrhs_ctx ctx, int nrhs);
 
 // Status helpers: record a message on the context and return the code.
 mrhs_status fail(mrhs_ctx ctx, mrhs_status st, const char* fmt, ...);
@@ -193,6 +200,20 @@ bool launch_fine_residual_f32(const Geom& g, float kappa, const void* U, const v
 hipError_t launch_fine_f64(const Geom& g, int t_bc, int mode, double kappa, const void* U,
                            const void* A, const void* in, void* out, int nrhs, hipStream_t s,
                            const F64Walk* fw = nullptr);
+// Estimated time (arbitrary unit) of the walk of tile (Bx, By, Bz, Ts) that
+// keeps its block in LDS, -1 where that does not fit: the rounds of workgroups
+// that the registers and LDS of 256 CUs admit together, times the wavefronts
+// per SIMD in one, times the slices, times the rows from outside the block.
+// Its constants are fitted to the times of some 5000 shapes on lattices from
+// 8^4 to 24^4 with 1 to 64 right-hand sides: there the shape it puts first
+// takes 4 % longer than the fastest on average (at most 23 %), and the first
+// 24 hold one within 1 % (the tuner times 16).
+double staged_walk_cost(const Geom& g, const int tile[4], int nrhs, int R, int chunks, bool f64);
+// the count best of them, best first (R, T, chunks and walk set)
+std::vector<FineCfg> staged_walks(const Geom& g, int nrhs, bool f64, size_t count);
+// the untuned FP32 operator A - kappa H: the best of them (R = 0: none fits
+// and the tiled kernel runs)
+FineCfg fine_default(const Geom& g, int nrhs);
 // whether the FP64 walk's tile (B, Ts) divides the lattice
 bool f64_walk_fits(const Geom& g, const int tile[4], int nrhs);
 // D = A - kappa H in FP64 on an FP32 input field (widened exactly on load)

@@ -238,7 +238,7 @@ hipError_t apply_level(mrhs_mg mg, int l, void* out, const void* in, int n, mrhs
   mrhs_ctx ctx = mg->ctx;
   if (l == 0)
     return launch_fine_f32(ctx->g, ctx->t_bc, 0, (float)ctx->kappa, ctx->U32.p, ctx->A32.p, in, out, n, s,
-                           &ctx->fine_cfg[n]);
+                           fine_config(ctx, n));
   LevelData& L = mg->lv[l];
   if (!mfma_supported(L.ncomp) || cp == MRHS_F32) return coarse_apply_f32(mg, l, in, out, n, s);
   const float* scale = nullptr;
@@ -260,7 +260,7 @@ hipError_t residual_level(mrhs_mg mg, int l, void* r, const void* b, const void*
   mrhs_ctx ctx = mg->ctx;
   hipError_t e = hipSuccess;
   if (l == 0 && launch_fine_residual_f32(ctx->g, (float)ctx->kappa, ctx->U32.p, ctx->A32.p, x, b, r, n, s,
-                                         &ctx->fine_cfg[n], &e))
+                                         fine_config(ctx, n), &e))
     return e;
   e = apply_level(mg, l, p, x, n, cp, s);
   if (e == hipSuccess) e = launch_sub(0, r, b, p, level_rows(mg, l) * n, s);
@@ -1027,7 +1027,7 @@ mrhs_status mrhs_mg_solve(mrhs_mg mg, void* x, const void* b, int32_t nrhs, cons
       void* w = k32 ? st->w32.p : st->w64.p;
       if (k32)
         SOLVER_HIP(launch_fine_f32(ctx->g, ctx->t_bc, 0, (float)ctx->kappa, ctx->U32.p, ctx->A32.p, Zj(j), w, n, ss,
-                                   &ctx->fine_cfg[n]));
+                                   fine_config(ctx, n)));
       else
         SOLVER_HIP(launch_fine_f64_in32(ctx->g, ctx->kappa, ctx->U64.p, ctx->A64.p, Zj(j), w, n, ss,
                                         &ctx->fine_cfg[n]));

@@ -1,6 +1,7 @@
 // Autotuner of the FP32 fine Wilson-clover kernel: for each requested Nrhs it
 // times launch configurations -- traversal tile and tile order, or the t-walk
-// kernel with its spatial block and time slices per thread, right-hand
+// kernel with its spatial block and time slices per thread (its block in LDS
+// where that fits one workgroup), right-hand
 // sides per thread (1, 2, 4), RHS chunks swept in turn (1, 2, 4; the tiles
 // are scanned again if chunking wins), a cap on resident workgroups per CU,
 // register budget, ordinary or non-temporal output stores -- on scratch
@@ -93,6 +94,12 @@ std::vector<std::array<int, 4>> walk_candidates(const Geom& g) {
     }
   return out;
 }
+
+// Walks that keep their block in LDS, timed besides: the first of those that
+// fit, by estimated time.
+constexpr size_t kStagedTimed = 16;
+// a first time this much longer than the best so far ends a candidate
+constexpr float kTuneGiveUp = 1.25f;
 
 int runtime_version() {
   int v = 0;
@@ -234,6 +241,7 @@ mrhs_status mrhs_tune(mrhs_ctx ctx, const int32_t* nrhs_list, int32_t count, con
         float ms = 0.f;
         if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
         if (rep > 0) t.push_back(ms * 1000.f);  // the first launch is a warm-up
+        if (rep > 0 && t[0] > kTuneGiveUp * best.us) break;
       }
       if (err != hipSuccess) return err;
       std::sort(t.begin(), t.end());
@@ -270,8 +278,14 @@ mrhs_status mrhs_tune(mrhs_ctx ctx, const int32_t* nrhs_list, int32_t count, con
         }
       }
     };
-    scan_tiles(best);
-    if (e == hipSuccess) scan_walks(best);
+    const FineCfg plain = best;
+    for (FineCfg cfg : staged_walks(ctx->g, n, false, kStagedTimed))
+      for (cfg.nt = 0; cfg.nt < 2 && e == hipSuccess; ++cfg.nt) {
+        e = time_cfg(cfg);
+        if (e == hipSuccess && cfg.us < best.us) best = cfg;
+      }
+    if (e == hipSuccess) scan_tiles(plain);
+    if (e == hipSuccess) scan_walks(plain);
     // stages: 0 RHS per thread, 1 RHS chunks, 2 workgroups per CU, 3 register budget, 4 store kind
     for (int stage = 0; stage < 5 && e == hipSuccess; ++stage) {
       const FineCfg cur = best;
@@ -435,6 +449,8 @@ mrhs_status mrhs_tune(mrhs_ctx ctx, const int32_t* nrhs_list, int32_t count, con
                                     ctx->stream);
       for (int i = 0; i < count && e == hipSuccess; ++i) {
         const int n = nrhs_list[i];
+        F64Walk best;  // tiled
+        best.us = 1e30f;
         auto time64 = [&](const F64Walk& w, float& us) -> hipError_t {
           std::vector<float> t;
           hipError_t err = hipSuccess;
@@ -448,16 +464,20 @@ mrhs_status mrhs_tune(mrhs_ctx ctx, const int32_t* nrhs_list, int32_t count, con
             float ms = 0.f;
             if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
             if (rep > 0) t.push_back(ms * 1000.f);
+            if (rep > 0 && t[0] > kTuneGiveUp * best.us) break;
           }
           if (err != hipSuccess) return err;
           std::sort(t.begin(), t.end());
           us = t[t.size() / 2];
           return hipSuccess;
         };
-        F64Walk best;  // tiled
-        e = time64(best, best.us);
-        const float tiled = best.us;
-        for (const auto& t : walk_candidates(ctx->g)) {
+        float tiled = 0.f;
+        e = time64(best, tiled);
+        best.us = tiled;
+        std::vector<std::array<int, 4>> tiles;
+        for (const FineCfg& c : staged_walks(ctx->g, n, true, kStagedTimed)) tiles.push_back({c.T[0], c.T[1], c.T[2], c.T[3]});
+        for (const auto& t : walk_candidates(ctx->g)) tiles.push_back(t);
+        for (const auto& t : tiles) {
           if (e != hipSuccess) break;
           const int tile[4] = {t[0], t[1], t[2], t[3]};
           if (!f64_walk_fits(ctx->g, tile, n)) continue;

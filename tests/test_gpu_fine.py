@@ -385,3 +385,75 @@ def test_f64_walk_rejects_and_tunes(gpu_lib):
     ctx.dwc(y, x)
     torch.cuda.synchronize()
     assert torch.equal(y, y0)
+
+
+def _set_walk(torch, ctx, dims, path, n, R, tile, curve, nt, chunks):
+    arch = torch.cuda.get_device_properties(0).gcnArchName.split(":")[0]
+    path.write_text(f"{arch} {_hip_runtime_version()} {' '.join(map(str, dims))} {n} {R} {' '.join(map(str, tile))} "
+                    f"{curve} 0 {nt} {chunks} 0 1.0\n")
+    ctx.tune([n], str(path))
+
+
+@pytest.mark.parametrize(
+    "dims,n,R,tile,nt,chunks",
+    [
+        ((6, 10, 4, 6), 12, 2, (3, 5, 4, 3), 0, 1),  # a block that spans z; 360 of 384 threads
+        ((6, 10, 4, 6), 24, 2, (2, 2, 2, 6), 1, 2),  # two chunks, one run over the whole t extent
+        ((6, 10, 4, 6), 64, 2, (2, 2, 4, 1), 1, 1),  # 512 threads, runs of one slice
+        ((6, 10, 4, 6), 7, 1, (6, 10, 1, 2), 0, 1),  # one site wide where the lattice is not: not kept in LDS
+        ((6, 10, 4, 6), 7, 1, (3, 5, 4, 2), 1, 1),
+        ((5, 3, 9, 4), 3, 1, (5, 3, 3, 2), 0, 1),  # odd extents, three threads per site: up to six link words each
+        ((5, 3, 9, 4), 2, 1, (5, 3, 9, 4), 0, 1),  # the whole lattice in one block, up to nine
+        ((4, 2, 2, 2), 1, 1, (2, 2, 2, 1), 0, 1),  # eight sites, one wavefront
+        ((3, 3, 3, 5), 5, 1, (3, 3, 3, 5), 1, 1),
+    ],
+)
+def test_walk_with_its_block_in_lds(gpu_lib, tmp_path, dims, n, R, tile, nt, chunks):
+    """The t-walk whose workgroup keeps its block in LDS, over the edges of its
+    shapes: blocks that span the lattice or meet it at a face, odd extents,
+    partly filled workgroups, every count of staged links, chunks, short and
+    full runs; bit for bit the tiled kernel, in FP32 and FP64."""
+    import torch
+
+    U = synth.gauge_haar(dims, 1601)
+    A = O.clover_packed(U, dims, CSW, KAPPA)
+    ctx = _ctx(gpu_lib, dims, U)
+    psi = synth.spinor_source(dims, n, 1602, np.complex64)
+    x = _dev(torch, psi)
+    y0, y = torch.empty_like(x), torch.empty_like(x)
+    _set_walk(torch, ctx, dims, tmp_path / "tiled.txt", n, 1, (1, 1, 1, 1), 0, 0, 1)
+    ctx.dwc(y0, x)
+    _set_walk(torch, ctx, dims, tmp_path / "walk.txt", n, R, tile, 2, nt, chunks)
+    assert ctx.get_tuning(n)[0] == R and ctx.get_tuning(n)[1] == tile
+    ctx.dwc(y, x)
+    torch.cuda.synchronize()
+    assert torch.equal(y, y0)
+    assert rel_l2(y.cpu().numpy(), O.dwc(U, A, KAPPA, psi, dims)) < 1e-6
+    x64 = x.to(torch.complex128)
+    z0, z = torch.empty_like(x64), torch.empty_like(x64)
+    ctx.set_f64_walk(n, None)
+    ctx.dwc(z0, x64)
+    ctx.set_f64_walk(n, tile, nt)
+    ctx.dwc(z, x64)
+    torch.cuda.synchronize()
+    assert torch.equal(z, z0)
+    assert rel_l2(z.cpu().numpy(), O.dwc(U, A, KAPPA, psi.astype(np.complex128), dims)) < 1e-12
+
+
+@pytest.mark.parametrize("dims", [(8, 8, 8, 8), (5, 3, 9, 4), (6, 10, 4, 6), (2, 2, 2, 2), (7, 7, 7, 11), (16, 2, 4, 6)])
+def test_untuned_launch_is_the_tiled_result(gpu_lib, tmp_path, dims):
+    """Without tuning the shape comes from an estimate: whatever it picks gives
+    the tiled kernel's bits."""
+    import torch
+
+    U = synth.gauge_haar(dims, 1701)
+    ctx = _ctx(gpu_lib, dims, U)
+    for n in (1, 2, 3, 4, 5, 8, 12, 17, 30, 64):
+        x = _dev(torch, synth.spinor_source(dims, n, 1702 + n, np.complex64))
+        y0, y = torch.empty_like(x), torch.empty_like(x)
+        assert ctx.get_tuning(n)[0] == 0
+        ctx.dwc(y, x)
+        _set_walk(torch, ctx, dims, tmp_path / f"tiled{n}.txt", n, 1, (1, 1, 1, 1), 0, 0, 1)
+        ctx.dwc(y0, x)
+        torch.cuda.synchronize()
+        assert torch.equal(y, y0), n

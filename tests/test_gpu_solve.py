@@ -610,6 +610,26 @@ def test_vcycle_same_with_walk_and_fused_residual(small, tmp_path):
         assert torch.equal(z_tiled, z_walk), fine_eo
 
 
+@pytest.mark.parametrize("n,R,tile,nt", [(12, 2, (4, 4, 4, 2), 0), (16, 2, (2, 4, 2, 4), 1), (7, 1, (4, 4, 2, 2), 0),
+                                         (3, 1, (4, 4, 4, 4), 0), (2, 1, (4, 4, 4, 1), 0)])
+def test_vcycle_same_with_the_block_in_lds(small, tmp_path, n, R, tile, nt):
+    """The V-cycle's fine residuals from the t-walk that keeps its block in LDS
+    (the subtraction in its epilogue) equal those of the tiled kernel and a
+    separate subtraction, bit for bit."""
+    import torch
+
+    dims, U, A, ctx, mg = small
+    from test_gpu_fine import _set_walk
+
+    v = dev(synth.spinor_source(dims, n, 9450, np.complex64))
+    z = []
+    for i, (r, t, curve) in enumerate(((1, (1, 1, 1, 1), 0), (R, tile, 2))):
+        _set_walk(torch, ctx, dims, tmp_path / f"w{i}.txt", n, r, t, curve, nt, 1)
+        z.append(torch.empty_like(v))
+        mg.precondition(z[-1], v, nu_pre=1, nu_post=2, coarsest_iters=8, coarse_prec="bf16", fine_eo=False)
+    assert torch.equal(z[0], z[1])
+
+
 def test_solve_same_with_f64_walk(small):
     """The outer solver's FP64 residuals run the tiled FP64 kernel or the FP64
     t-walk; the two give the same bits, so the whole solve does too."""
