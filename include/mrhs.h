@@ -155,9 +155,11 @@ mrhs_status mrhs_hop_eo_apply(mrhs_ctx ctx, void* out, const void* in, int32_t n
  * time slice, carrying the backward t-hop in registers; Bx By Bz >= 16, the
  * block must divide the spatial extents and Ts divide Lt / 2) with
  * rhs_per_thread 1 or 2 (0: two for even nrhs, else one); tile = NULL
- * selects the tiled kernel.  mrhs_tune chooses it by timing (lattices with
- * even extents).  The fields computed are bit-identical either way.  An
- * invalid shape gets MRHS_ERR_INVALID_ARG. */
+ * selects the tiled kernel.  A walk whose block fits one workgroup keeps it in
+ * LDS.  mrhs_tune chooses the shape by timing (lattices with even extents);
+ * before either call it is the walk of the least estimated time, or the tiled
+ * kernel on small lattices.  The fields computed are bit-identical either way.
+ * An invalid shape gets MRHS_ERR_INVALID_ARG. */
 mrhs_status mrhs_set_eo_walk(mrhs_ctx ctx, int32_t nrhs, const int32_t* tile, int32_t rhs_per_thread);
 /* mrhs_get_eo_walk: the shape in use for nrhs (*on = 0: tiled kernel), and
  * the times the last mrhs_tune measured for it and for the tiled kernel

@@ -237,6 +237,12 @@ const FineCfg* fine_config(mrhs_ctx ctx, int nrhs) {
   return &ctx->fine_auto[nrhs];
 }
 
+const EoWalk* eo_config(mrhs_ctx ctx, int nrhs) {
+  if (ctx->eo_set[nrhs]) return &ctx->eo_walk[nrhs];
+  std::call_once(ctx->eo_auto_once[nrhs], [&] { ctx->eo_auto[nrhs] = eo_default(ctx->g, nrhs); });
+  return &ctx->eo_auto[nrhs];
+}
+
 const int* fine_order_table(mrhs_ctx ctx, const int T[4], int curve) {
   std::array<int, 5> key{T[0], T[1], T[2], T[3], curve};
   for (auto& o : ctx->orders)
@@ -494,7 +500,7 @@ mrhs_status mrhs_hop_eo_apply(mrhs_ctx ctx, void* out, const void* in, int32_t n
   MRHS_HIP(ctx, launch_hop_eo(p64, ctx->g.V / 2, static_cast<const int4*>(ctx->eo_tab[out_parity].p),
                               static_cast<const int*>(ctx->eo_order[out_parity].p), p64 ? ctx->U64.p : ctx->U32.p,
                               in, out, nrhs, ctx->stream, 0, nullptr, nullptr, 0.0, &ctx->g, out_parity,
-                              &ctx->eo_walk[nrhs]));
+                              eo_config(ctx, nrhs)));
   return MRHS_OK;
 }
 
@@ -512,6 +518,7 @@ mrhs_status mrhs_set_eo_walk(mrhs_ctx ctx, int32_t nrhs, const int32_t* tile, in
     w.Ts = tile[3];
   }
   ctx->eo_walk[nrhs] = w;
+  ctx->eo_set[nrhs] = true;
   ctx->op_gen++;  // captured V-cycles hold the launch shape
   return MRHS_OK;
 }
@@ -520,7 +527,7 @@ mrhs_status mrhs_get_eo_walk(mrhs_ctx ctx, int32_t nrhs, int32_t* on, int32_t* r
                              float* us, float* us_tiled) {
   if (!ctx) return MRHS_ERR_INVALID_ARG;
   if (nrhs < 1 || nrhs > MRHS_MAX_NRHS) return fail(ctx, MRHS_ERR_SHAPE, "nrhs = %d outside [1, %d]", nrhs, MRHS_MAX_NRHS);
-  const EoWalk& w = ctx->eo_walk[nrhs];
+  const EoWalk& w = *eo_config(ctx, nrhs);
   if (on) *on = w.on;
   if (rhs_per_thread) *rhs_per_thread = w.R;
   if (tile) {
@@ -606,9 +613,9 @@ mrhs_status mrhs_schur_apply(mrhs_ctx ctx, void* out, const void* in, int32_t nr
   const auto* oe = static_cast<const int*>(ctx->eo_order[0].p);
   const auto* oo = static_cast<const int*>(ctx->eo_order[1].p);
   MRHS_HIP(ctx, launch_hop_eo(p64, nh, to, oo, U, in, t2, nrhs, ctx->stream, 1, p64 ? ctx->Ainv64.p : ctx->Ainv32.p,
-                              nullptr, 0.0, &ctx->g, 1, &ctx->eo_walk[nrhs]));
+                              nullptr, 0.0, &ctx->g, 1, eo_config(ctx, nrhs)));
   MRHS_HIP(ctx, launch_hop_eo(p64, nh, te, oe, U, t2, out, nrhs, ctx->stream, 2, p64 ? ctx->A64.p : ctx->A32.p, in,
-                              -ctx->kappa * ctx->kappa, &ctx->g, 0, &ctx->eo_walk[nrhs]));
+                              -ctx->kappa * ctx->kappa, &ctx->g, 0, eo_config(ctx, nrhs)));
   return MRHS_OK;
 }
 

@@ -144,6 +144,9 @@ struct mrhs_ctx_s {
   mrhs::FineCfg fine_auto[MRHS_MAX_NRHS + 1];
   std::once_flag fine_auto_once[MRHS_MAX_NRHS + 1];
   mrhs::EoWalk eo_walk[MRHS_MAX_NRHS + 1];
+  bool eo_set[MRHS_MAX_NRHS + 1] = {};  // by mrhs_tune or mrhs_set_eo_walk; else eo_auto, worked out on first use
+  mrhs::EoWalk eo_auto[MRHS_MAX_NRHS + 1];
+  std::once_flag eo_auto_once[MRHS_MAX_NRHS + 1];
   mrhs::F64Walk f64_walk[MRHS_MAX_NRHS + 1];
 
   // checkerboard tables (per parity, four int4 per site, and the traversal
@@ -163,6 +166,8 @@ namespace mrhs {
 
 // The launch configuration of the FP32 operator A - kappa H at nrhs.
 const FineCfg* fine_config(mrhs_ctx ctx, int nrhs);
+// and of its checkerboard hop
+const EoWalk* eo_config(mrhs_ctx ctx, int nrhs);
 
 // Status helpers: record a message on the context and return the code.
 mrhs_status fail(mrhs_ctx ctx, mrhs_status st, const char* fmt, ...);
@@ -211,6 +216,10 @@ hipError_t launch_fine_f64(const Geom& g, int t_bc, int mode, double kappa, cons
 double staged_walk_cost(const Geom& g, const int tile[4], int nrhs, int R, int chunks, bool f64);
 // the count best of them, best first (R, T, chunks and walk set)
 std::vector<FineCfg> staged_walks(const Geom& g, int nrhs, bool f64, size_t count);
+// and of the checkerboard hop's walks that do (FP32)
+std::vector<EoWalk> staged_eo_walks(const Geom& g, int nrhs, size_t count);
+// the untuned checkerboard hop (FP32)
+EoWalk eo_default(const Geom& g, int nrhs);
 // the untuned FP32 operator A - kappa H: the best of them (R = 0: none fits
 // and the tiled kernel runs)
 FineCfg fine_default(const Geom& g, int nrhs);

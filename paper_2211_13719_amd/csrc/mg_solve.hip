@@ -329,7 +329,7 @@ hipError_t eo_smooth(mrhs_mg mg, SolverState* st, void* x, void* r, const void* 
   // rhat = r_e + kappa H_eo (A_o^-1 r_o), reading r's rows in place
   hipError_t e = launch_clover_eo(0, nh, tabo, Ai, r, nullptr, 0.0, to, n, s, true);
   const Geom* g = &ctx->g;
-  const EoWalk* ew = &ctx->eo_walk[n];
+  const EoWalk* ew = eo_config(ctx, n);
   if (e == hipSuccess) e = launch_hop_eo(0, nh, tabe, orde, U, to, rho, n, s, 3, nullptr, r, k, g, 0, ew);
   if (e == hipSuccess) e = launch_zero(ee, hb, s);
   for (int i = 0; i < nu && e == hipSuccess; ++i) {

@@ -361,6 +361,8 @@ mrhs_status mrhs_tune(mrhs_ctx ctx, const int32_t* nrhs_list, int32_t count, con
     char* half2 = static_cast<char*>(out.p) + (size_t)nhalf * 12 * nmax * 8;  // second half of out
     for (int i = 0; i < count && e == hipSuccess; ++i) {
       const int n = nrhs_list[i];
+      EoWalk best;  // tiled
+      best.us = 1e30f;
       auto time_eo = [&](const EoWalk& w, float& us) -> hipError_t {
         std::vector<float> t;
         hipError_t err = hipSuccess;
@@ -378,16 +380,18 @@ mrhs_status mrhs_tune(mrhs_ctx ctx, const int32_t* nrhs_list, int32_t count, con
           float ms = 0.f;
           if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
           if (rep > 0) t.push_back(ms * 1000.f);
+          if (rep > 0 && t[0] > kTuneGiveUp * best.us) break;
         }
         if (err != hipSuccess) return err;
         std::sort(t.begin(), t.end());
         us = t[t.size() / 2];
         return hipSuccess;
       };
-      EoWalk best;  // tiled
-      e = time_eo(best, best.us);
-      const float tiled = best.us;
-      // coordinate descent: spatial block at a short run, then the run length, then R
+      float tiled = 0.f;
+      e = time_eo(best, tiled);
+      best.us = tiled;
+      // the walks with their block in LDS, by estimated time, then those
+      // without by coordinate descent: spatial block at a short run, then the run length, then R
       const int Lh = ctx->g.L[3] / 2;
       const int ts0 = Lh % 4 == 0 ? 4 : (Lh % 2 == 0 ? 2 : 1);
       const std::array<int, 3> blocks[] = {{4, 4, 4}, {8, 4, 4}, {8, 8, 4}, {6, 6, 4}, {12, 4, 4},
@@ -398,6 +402,7 @@ mrhs_status mrhs_tune(mrhs_ctx ctx, const int32_t* nrhs_list, int32_t count, con
         e = time_eo(w, w.us);
         if (e == hipSuccess && w.us < best.us) best = w;
       };
+      for (const EoWalk& w : staged_eo_walks(ctx->g, n, kStagedTimed)) consider(w);
       for (const auto& b : blocks) {
         EoWalk w;
         w.on = 1;
@@ -426,6 +431,7 @@ mrhs_status mrhs_tune(mrhs_ctx ctx, const int32_t* nrhs_list, int32_t count, con
         best.us_tiled = tiled;
         if (!best.on) best.us = tiled;
         ctx->eo_walk[n] = best;
+        ctx->eo_set[n] = true;
       }
     }
     (void)hipStreamSynchronize(ctx->stream);

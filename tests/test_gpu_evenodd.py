@@ -265,6 +265,57 @@ def test_hop_eo_walk_bitwise(lat, walk, R, nrhs):
     ctx.set_eo_walk(nrhs, None)
 
 
+@pytest.mark.parametrize("nrhs,walk,R", [
+    (24, (4, 2, 2, 1), 2),  # runs of one output site
+    (24, (2, 6, 2, 4), 2),  # one run over the whole t extent
+    (64, (4, 2, 2, 2), 2),  # two chunks of right-hand sides
+    (6, (2, 3, 4, 2), 1),   # a block that spans z, of odd extent in y; more than three link words per thread
+    (13, (4, 3, 2, 4), 1),
+    (48, (4, 2, 4, 2), 1),  # four chunks
+])
+def test_hop_eo_walk_with_its_block_in_lds(lat, nrhs, walk, R):
+    """The checkerboard walk that keeps its block in LDS: the tiled kernel's
+    fields bit for bit, both parities and the Schur launches."""
+    import torch
+
+    dims, U, A, ctx = lat
+    hops = [dev(EO.to_cb(synth.spinor_source(dims, nrhs, 70 + p, np.complex64), dims, 1 - p)) for p in (0, 1)]
+    chi = dev(EO.to_cb(synth.spinor_source(dims, nrhs, 80, np.complex64), dims, 0))
+    out = []
+    for tile, r in ((None, 0), (walk, R)):
+        ctx.set_eo_walk(nrhs, tile, r)
+        o = [torch.empty_like(chi) for _ in range(3)]
+        for p in (0, 1):
+            ctx.hop_eo(o[p], hops[p], p)
+        ctx.schur(o[2], chi)
+        out.append(o)
+    torch.cuda.synchronize()
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+    ctx.set_eo_walk(nrhs, None)
+
+
+@pytest.mark.parametrize("dims", [(8, 8, 8, 8), (4, 6, 10, 4), (2, 2, 2, 4), (12, 4, 8, 16)])
+def test_untuned_hop_eo_is_the_tiled_result(gpu_lib, dims):
+    """Without tuning the checkerboard hop's shape comes from an estimate:
+    whatever it picks gives the tiled kernel's bits."""
+    import torch
+
+    U = synth.gauge_haar(dims, 4100)
+    ctx = gpu_lib.Context(dims, t_bc=-1)
+    ctx.set_gauge(U)
+    ctx.build_clover(CSW, KAPPA)
+    for n in (1, 4, 7, 12, 24, 32, 64):
+        chi = dev(EO.to_cb(synth.spinor_source(dims, n, 4101, np.complex64), dims, 0))
+        a, b = torch.empty_like(chi), torch.empty_like(chi)
+        ctx.schur(a, chi)
+        ctx.set_eo_walk(n, None)
+        ctx.schur(b, chi)
+        torch.cuda.synchronize()
+        assert torch.equal(a, b), n
+    ctx.close()
+
+
 def test_eo_walk_rejects_bad_shapes(lat, gpu_lib):
     dims, U, A, ctx = lat
     for tile, R in [((4, 4, 4, 1), 0), ((2, 2, 2, 1), 0), ((4, 6, 4, 3), 0), ((4, 6, 4, 1), 2), ((4, 6, 4, 1), 3)]:

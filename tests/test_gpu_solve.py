@@ -300,6 +300,30 @@ def test_even_odd_smoother_alone(gpu_lib, dims, block, nv, nrhs, walk):
     ctx.close()
 
 
+@pytest.mark.parametrize("nrhs,tile,R", [(24, (4, 4, 2, 2), 2), (64, (4, 2, 2, 2), 2), (6, (4, 4, 2, 4), 1),
+                                         (48, (2, 4, 4, 1), 1)])
+def test_even_odd_smoother_with_the_block_in_lds(gpu_lib, nrhs, tile, R):
+    """As test_even_odd_smoother_alone, the hops being the walk that keeps its
+    block in LDS: its partial sums with one and two right-hand sides per thread
+    and over several chunks of them."""
+    import torch
+
+    dims = (8, 8, 8, 8)
+    U = synth.gauge_haar(dims, 4242)
+    A = O.clover_packed(U, dims, CSW, KAPPA)
+    ctx, mg = build(gpu_lib, dims, U, [(4, 4, 4, 4)], [16], setup_iters=1, smooth_steps=4)
+    ctx.set_eo_walk(nrhs, tile, R)
+    v = synth.spinor_source(dims, nrhs, 9301, np.complex64)
+    z = torch.empty(v.shape, dtype=torch.complex64, device="cuda")
+    mg.precondition(z, dev(v), nu_pre=0, nu_post=3, coarsest_iters=0, coarse_prec="bf16", fine_eo=True)
+    want = _eo_smoother_ref(U, A, KAPPA, v, dims, 3)
+    got = z.cpu().numpy()
+    for k in range(nrhs):
+        assert np.linalg.norm(got[:, :, k] - want[:, :, k]) < 1e-5 * np.linalg.norm(want[:, :, k]), k
+    mg.close()
+    ctx.close()
+
+
 @pytest.mark.timeout(1200)
 def test_solve_24x24x24x128_bench_settings(gpu_lib, capsys, tmp_path):
     """The solve workload the benchmark times (24^3 x 128 smooth links at the
