@@ -714,16 +714,8 @@ mrhs_status mrhs_axpy(mrhs_ctx ctx, void* y, const double* alpha, const void* x,
   st = check_field_args(ctx, y, x, nrhs, prec, (size_t)ncomp, nsites);
   if (st != MRHS_OK) return st;
   DeviceGuard dg(ctx->device);
-  const void* al = alpha;
-  if (!alpha_on_device) {
-    st = ensure(ctx, ctx->scal, (size_t)nrhs * 16);
-    if (st != MRHS_OK) return st;
-    MRHS_HIP(ctx, hipMemcpyAsync(ctx->scal.p, alpha, (size_t)nrhs * 16, hipMemcpyHostToDevice, ctx->stream));
-    al = ctx->scal.p;
-  }
-  hipError_t e = launch_axpy(prec == MRHS_F64, y, al, x, (long)nsites * ncomp, nrhs, ctx->stream);
+  hipError_t e = launch_axpy(prec == MRHS_F64, y, alpha, alpha_on_device != 0, x, (long)nsites * ncomp, nrhs, ctx->stream);
   if (e != hipSuccess) return hip_fail(ctx, e, "axpy launch");
-  if (!alpha_on_device) MRHS_HIP(ctx, hipStreamSynchronize(ctx->stream));  // alpha's host memory may be reused
   return MRHS_OK;
 }
 

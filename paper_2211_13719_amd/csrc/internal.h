@@ -279,9 +279,9 @@ hipError_t launch_dot(int prec64, int mode, const void* a, const void* b, long r
 // out (double2[m][nrhs]) = <v_j, w>
 hipError_t launch_multi_dot(int prec64, const void* const* v, int m, const void* w, long rows, int nrhs,
                             void* out, void* scratch, hipStream_t s);
-// y += alpha (double2[nrhs] on the device) * x
-hipError_t launch_axpy(int prec64, void* y, const void* alpha_dev, const void* x, long rows, int nrhs,
-                       hipStream_t s);
+// y += alpha * x, alpha nrhs complex doubles on the device or on the host (read before the call returns)
+hipError_t launch_axpy(int prec64, void* y, const double* alpha, bool alpha_on_device, const void* x, long rows,
+                       int nrhs, hipStream_t s);
 
 // ---- launchers (intergrid.hip) ------------------------------------------------
 bool intergrid_supported(int nv, int h);

@@ -106,6 +106,40 @@ def test_axpy(ctx, dt):
     assert np.linalg.norm(got - want) / np.linalg.norm(want) < tol
 
 
+@pytest.mark.parametrize("dt", [np.complex64, np.complex128])
+@pytest.mark.parametrize("n", [1, 2, 7, 64])
+def test_axpy_host_and_device_coefficients(ctx, n, dt):
+    """Coefficients held by the launch (host) and read from memory (device)
+    give the same bits, one rounding of the FP64 update (half an ulp per
+    component), whatever the column count; the host array may change at once."""
+    import ctypes as C
+
+    import torch
+
+    from paper_2211_13719_amd._lib import lib
+
+    ns, nc = 331, 12
+    x = synth.coarse_source(ns, nc, n, 3, dt)
+    y = synth.coarse_source(ns, nc, n, 4, dt)
+    alpha = synth.gaussian_complex(synth.rng(5), (n,))
+    want = y.astype(np.complex128) + alpha[None, None, :] * x.astype(np.complex128)
+    tx, ty, tz = _dev(torch, x), _dev(torch, y), _dev(torch, y)
+    a = alpha.copy()
+    ctx.axpy(ty, a, tx)
+    a[:] = np.nan
+    ta = _dev(torch, alpha)
+    from paper_2211_13719_amd import F32, F64
+
+    prec = F64 if dt == np.complex128 else F32
+    assert lib.mrhs_axpy(ctx._h, C.c_void_p(tz.data_ptr()), C.c_void_p(ta.data_ptr()), C.c_void_p(tx.data_ptr()), ns, nc,
+                         n, prec, 1) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(ty, tz)
+    got = ty.cpu().numpy()
+    tol = 2.0 ** -24 * 1.01 if dt == np.complex64 else 1e-15
+    assert np.linalg.norm(got - want) <= tol * np.linalg.norm(want)
+
+
 def test_blas_rejects_bad_args(ctx, gpu_lib):
     import torch
 
