@@ -2317,7 +2317,7 @@ double staged_walk_cost(const Geom& g, const int tile[4], int nrhs, int R, int c
   return staged_cost(w, R, f64);
 }
 
-std::vector<EoWalk> staged_eo_walks(const Geom& g, int nrhs, size_t count) {
+std::vector<EoWalk> staged_eo_walks(const Geom& g, int nrhs, size_t count, double* cost) {
   std::vector<std::pair<double, EoWalk>> all;
   for (int R = 1; R <= 2; ++R) {
     if (nrhs % R) continue;
@@ -2340,18 +2340,23 @@ std::vector<EoWalk> staged_eo_walks(const Geom& g, int nrhs, size_t count) {
           }
   }
   std::stable_sort(all.begin(), all.end(), [](const auto& a, const auto& b) { return a.first < b.first; });
+  if (cost && !all.empty()) *cost = all[0].first;
   std::vector<EoWalk> out;
   for (size_t i = 0; i < all.size() && i < count; ++i) out.push_back(all[i].second);
   return out;
 }
 
-// The first of them if its runs have two output sites or more: against the
-// tiled kernel 0.67 to 1.02 of the time on 16^3 x 32, 20x14x12x16 and 24^4 with
-// 4 to 64 right-hand sides, whereas runs of one, which small lattices are cut
-// into to fill the device, took 0.97 to 1.58 of it.
+// The first of them on fields beyond the caches (2^20 rows of one right-hand
+// side: 48 MiB of each checkerboard field) unless the lattice's divisors cut it
+// badly (estimate per site).  Of 260 drawn lattices and batches the first
+// against the tiled kernel took 0.73 to 0.96 of the time there, and 0.8 to 1.5
+// on smaller fields, whose rows the tiled kernel finds in the caches.
 EoWalk eo_default(const Geom& g, int nrhs) {
-  const std::vector<EoWalk> w = staged_eo_walks(g, nrhs, 1);
-  return !w.empty() && w[0].Ts >= 2 ? w[0] : EoWalk{};
+  const double rows = (double)g.V * nrhs;
+  if (rows < 1 << 20) return EoWalk{};
+  double cost = 0.0;
+  const std::vector<EoWalk> w = staged_eo_walks(g, nrhs, 1, &cost);
+  return !w.empty() && cost < 1.55e-5 * rows ? w[0] : EoWalk{};
 }
 
 // Every staged walk of the lattice, as f(tile, R, chunks, cost).
@@ -2400,6 +2405,22 @@ FineCfg fine_default(const Geom& g, int nrhs) {
     best.chunks = chunks;
     for (int m = 0; m < 4; ++m) best.T[m] = tile[m];
   });
+  // Against the tiled kernel, on 260 drawn lattices and batches without tuning:
+  // even batches below 8 took 0.44 to 1.05 of its time, fields of 3e5 rows and
+  // more of one right-hand side 0.57 to 1.06.  On smaller fields, whose rows the
+  // tiled kernel finds in the caches, and for odd batches it took up to 1.3 where
+  // the lattice's divisors cut it badly: there both times are estimated (fits
+  // to the same draws, microseconds) and a lead is asked for.  One right-hand
+  // side: 1.04 on average up to 5e4 sites, 0.97 at 16^3 x 32 and 0.54 at 24^4.
+  const double V = g.V, rows = V * nrhs, staged = 3.8 * cost - 0.5;
+  bool take = true;
+  if (nrhs == 1)
+    take = g.V >= 1 << 17;
+  else if (nrhs % 2)
+    take = staged < 0.9 * (6.6 + 96.4e-6 * rows + 159e-6 * V);
+  else if (nrhs >= 8 && rows < 3e5)
+    take = staged < 0.75 * (9.0 + 62.7e-6 * rows + 358e-6 * V);
+  if (!take) return FineCfg{};
   // chunks of 16 and more write whole 128-byte lines, which need not stay in
   // the cache; non-temporal stores of less than a line cost up to a tenth
   best.nt = best.R && nrhs / best.chunks >= 16;

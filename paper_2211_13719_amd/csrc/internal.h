@@ -217,11 +217,11 @@ double staged_walk_cost(const Geom& g, const int tile[4], int nrhs, int R, int c
 // the count best of them, best first (R, T, chunks and walk set)
 std::vector<FineCfg> staged_walks(const Geom& g, int nrhs, bool f64, size_t count);
 // and of the checkerboard hop's walks that do (FP32)
-std::vector<EoWalk> staged_eo_walks(const Geom& g, int nrhs, size_t count);
+std::vector<EoWalk> staged_eo_walks(const Geom& g, int nrhs, size_t count, double* cost = nullptr);
 // the untuned checkerboard hop (FP32)
 EoWalk eo_default(const Geom& g, int nrhs);
-// the untuned FP32 operator A - kappa H: the best of them (R = 0: none fits
-// and the tiled kernel runs)
+// the untuned FP32 operator A - kappa H: the best of them, or R = 0 for the
+// tiled kernel
 FineCfg fine_default(const Geom& g, int nrhs);
 // whether the FP64 walk's tile (B, Ts) divides the lattice
 bool f64_walk_fits(const Geom& g, const int tile[4], int nrhs);
