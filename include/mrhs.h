@@ -236,9 +236,11 @@ mrhs_status mrhs_read_probe(mrhs_ctx ctx, const void* buf, int64_t bytes, int32_
                             float* ms);
 
 /* mrhs_axpy: y_k <- y_k + alpha_k x_k per column, alpha_k = alpha[2k] + i alpha[2k+1]
- * (FP64, host memory if alpha_on_device = 0, read before the call returns, else
- * device memory); the update
- * is computed in FP64 and rounded to prec.  x and y must not overlap. */
+ * (FP64, host memory if alpha_on_device = 0, else device memory); the update
+ * is computed in FP64 and rounded to prec.  x and y must not overlap.  Host
+ * coefficients may be reused once the call returns.  Those in pinned or managed
+ * memory are read in stream order, and the call synchronises; others are read
+ * by the call itself. */
 mrhs_status mrhs_axpy(mrhs_ctx ctx, void* y, const double* alpha, const void* x, int64_t nsites, int32_t ncomp,
                       int32_t nrhs, mrhs_prec prec, int32_t alpha_on_device);
 

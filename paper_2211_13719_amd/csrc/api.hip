@@ -655,6 +655,16 @@ mrhs_status reduce_to(mrhs_ctx ctx, double* out, int out_on_device, size_t bytes
   return MRHS_OK;
 }
 
+// Whether p lies in memory of the HIP runtime (pinned, managed or device).
+bool known_to_hip(const void* p) {
+  hipPointerAttribute_t a;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type != hipMemoryTypeUnregistered;
+}
+
 }  // namespace
 
 extern "C" {
@@ -714,8 +724,20 @@ mrhs_status mrhs_axpy(mrhs_ctx ctx, void* y, const double* alpha, const void* x,
   st = check_field_args(ctx, y, x, nrhs, prec, (size_t)ncomp, nsites);
   if (st != MRHS_OK) return st;
   DeviceGuard dg(ctx->device);
-  hipError_t e = launch_axpy(prec == MRHS_F64, y, alpha, alpha_on_device != 0, x, (long)nsites * ncomp, nrhs, ctx->stream);
+  // Host coefficients that work on the stream can still be filling (pinned or
+  // managed memory, the target of an asynchronous copy or of a kernel) are read
+  // in stream order; other host memory is read here, by the launch itself.
+  const bool ordered = !alpha_on_device && known_to_hip(alpha);
+  const double* al = alpha;
+  if (ordered) {
+    st = ensure(ctx, ctx->scal, (size_t)nrhs * 16);
+    if (st != MRHS_OK) return st;
+    MRHS_HIP(ctx, hipMemcpyAsync(ctx->scal.p, alpha, (size_t)nrhs * 16, hipMemcpyDefault, ctx->stream));
+    al = static_cast<const double*>(ctx->scal.p);
+  }
+  hipError_t e = launch_axpy(prec == MRHS_F64, y, al, ordered || alpha_on_device, x, (long)nsites * ncomp, nrhs, ctx->stream);
   if (e != hipSuccess) return hip_fail(ctx, e, "axpy launch");
+  if (ordered) MRHS_HIP(ctx, hipStreamSynchronize(ctx->stream));  // alpha's memory may be reused
   return MRHS_OK;
 }
 

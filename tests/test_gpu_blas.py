@@ -140,6 +140,26 @@ def test_axpy_host_and_device_coefficients(ctx, n, dt):
     assert np.linalg.norm(got - want) <= tol * np.linalg.norm(want)
 
 
+def test_axpy_pinned_coefficients_in_stream_order(ctx):
+    """Host coefficients in pinned memory that an earlier copy on the stream is
+    still filling are read after that copy, and may be overwritten as soon as
+    the call returns."""
+    import torch
+
+    n = 8
+    x = torch.ones(100, 12, n, dtype=torch.complex64, device="cuda")
+    y = torch.zeros_like(x)
+    src = torch.full((n,), 5.0, dtype=torch.complex128, device="cuda")
+    alpha = torch.zeros(n, dtype=torch.complex128, pin_memory=True)
+    torch.cuda.synchronize()
+    torch.cuda._sleep(20_000_000)
+    alpha.copy_(src, non_blocking=True)
+    ctx.axpy(y, alpha.numpy(), x)
+    alpha.fill_(7.0)
+    torch.cuda.synchronize()
+    assert torch.all(y == 5.0)
+
+
 def test_blas_rejects_bad_args(ctx, gpu_lib):
     import torch
 
