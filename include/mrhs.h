@@ -240,7 +240,8 @@ mrhs_status mrhs_read_probe(mrhs_ctx ctx, const void* buf, int64_t bytes, int32_
  * is computed in FP64 and rounded to prec.  x and y must not overlap.  Host
  * coefficients may be reused once the call returns.  Those in pinned or managed
  * memory are read in stream order, and the call synchronises; others are read
- * by the call itself. */
+ * by the call itself.  Under stream capture host coefficients get
+ * MRHS_ERR_HIP. */
 mrhs_status mrhs_axpy(mrhs_ctx ctx, void* y, const double* alpha, const void* x, int64_t nsites, int32_t ncomp,
                       int32_t nrhs, mrhs_prec prec, int32_t alpha_on_device);
 

@@ -724,6 +724,11 @@ mrhs_status mrhs_axpy(mrhs_ctx ctx, void* y, const double* alpha, const void* x,
   st = check_field_args(ctx, y, x, nrhs, prec, (size_t)ncomp, nsites);
   if (st != MRHS_OK) return st;
   DeviceGuard dg(ctx->device);
+  // A graph would hold the values that host coefficients have now.
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (!alpha_on_device) MRHS_HIP(ctx, hipStreamIsCapturing(ctx->stream, &cap));
+  if (cap != hipStreamCaptureStatusNone)
+    return fail(ctx, MRHS_ERR_HIP, "axpy: host coefficients under stream capture; pass them in device memory");
   // Host coefficients that work on the stream can still be filling (pinned or
   // managed memory, the target of an asynchronous copy or of a kernel) are read
   // in stream order; other host memory is read here, by the launch itself.

@@ -160,6 +160,39 @@ def test_axpy_pinned_coefficients_in_stream_order(ctx):
     assert torch.all(y == 5.0)
 
 
+def test_axpy_host_coefficients_refused_under_capture(gpu_lib):
+    """A captured graph would replay the values that host coefficients had at
+    capture: the call is refused, device coefficients are captured."""
+    import ctypes as C
+
+    import torch
+
+    from paper_2211_13719_amd import F32
+    from paper_2211_13719_amd._lib import lib
+
+    n = 4
+    c = gpu_lib.Context((4, 4, 4, 4), t_bc=-1)
+    stream = torch.cuda.Stream()
+    c.set_stream(stream)
+    x = torch.ones(10, 12, n, dtype=torch.complex64, device="cuda")
+    y = torch.zeros_like(x)
+    alpha = torch.full((n,), 3.0, dtype=torch.complex128, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        with pytest.raises(gpu_lib.MrhsError):
+            c.axpy(y, np.full(n, 2.0 + 0j), x)
+        st = lib.mrhs_axpy(c._h, C.c_void_p(y.data_ptr()), C.c_void_p(alpha.data_ptr()), C.c_void_p(x.data_ptr()), 10, 12,
+                           n, F32, 1)
+    assert st == 0
+    for k in (1, 2):
+        alpha.fill_(3.0 * k)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.all(y == 3.0 * (2 * k - 1))
+    c.close()
+
+
 def test_blas_rejects_bad_args(ctx, gpu_lib):
     import torch
 
