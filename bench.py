@@ -92,7 +92,7 @@ FINE_SOURCES = ("fine.hip", "internal.h", "api.hip")
 # it only while the kernel name, sources and configurations still match.
 FINE_TRAFFIC = {
     "kernel": "fine_walk_kernel<2, 0, false>",
-    "sources": "bbef1fda7b7c2235",
+    "sources": "b9c23099dc21393a",
     "configs": {"12": [2, [3, 3, 8, 6], 128], "24": [2, [6, 3, 2, 12], 132], "48": [2, [3, 3, 2, 24], 132],
                 "64": [2, [4, 2, 2, 12], 132]},
     "bytes_per_launch": 4.692e9,
@@ -135,7 +135,8 @@ def fine_kernel_name(ctx, n):
         words = next((i for i in range(1 if R == 2 else 3)
                       if 18 * bs <= (3, 6, 9)[i] * threads and 9 * faces <= (2, 4, 4)[i] * threads), None)
         thin = any(tile[m] == 1 < DIMS[m] for m in range(3))
-        if not occ and words is not None and threads <= 512 and not thin:  # its block in LDS
+        few = R == 2 and chunks * int(np.prod(DIMS)) // int(np.prod(tile)) <= 128
+        if not occ and words is not None and threads <= 512 and not thin and not few:  # its block in LDS
             return f"fine_walk_kernel<{R}, {words}, false>"
         return f"fine_walk_open_kernel<{R}, {occ}, false>"
     return f"fine_kernel<float, {R}, 0, true, true, {occ}, HIP_vector_type<float, 2u> >"

@@ -156,10 +156,11 @@ mrhs_status mrhs_hop_eo_apply(mrhs_ctx ctx, void* out, const void* in, int32_t n
  * block must divide the spatial extents and Ts divide Lt / 2) with
  * rhs_per_thread 1 or 2 (0: two for even nrhs, else one); tile = NULL
  * selects the tiled kernel.  A walk whose block fits one workgroup keeps it in
- * LDS.  mrhs_tune chooses the shape by timing (lattices with even extents);
- * before either call it is the walk of the least estimated time, or the tiled
- * kernel on small lattices.  The fields computed are bit-identical either way.
- * An invalid shape gets MRHS_ERR_INVALID_ARG. */
+ * LDS where that is estimated to be faster.  mrhs_tune chooses the shape by
+ * timing (lattices with even extents); before either call it is the walk of
+ * the least estimated time, or the tiled kernel on small lattices and those
+ * whose extents cut badly into blocks.  The fields computed are bit-identical
+ * either way.  An invalid shape gets MRHS_ERR_INVALID_ARG. */
 mrhs_status mrhs_set_eo_walk(mrhs_ctx ctx, int32_t nrhs, const int32_t* tile, int32_t rhs_per_thread);
 /* mrhs_get_eo_walk: the shape in use for nrhs (*on = 0: tiled kernel), and
  * the times the last mrhs_tune measured for it and for the tiled kernel
@@ -513,9 +514,10 @@ mrhs_status mrhs_mg_solve(mrhs_mg mg, void* x, const void* b, int32_t nrhs, cons
  * slices, one per XCD, and columns of the full time extent), two tile orders
  * (lexicographic, Morton), or the t-walk kernel (each thread walks a run of
  * time slices of one site of a spatial block, carrying its t-neighbours in
- * registers; a block that fits one workgroup is kept in LDS) with its block
- * and run length, the right-hand sides split into 1, 2 or 4 chunks
- * swept one after the other, at most 1, 2 or 3 workgroups per CU or no limit,
+ * registers; a block that fits one workgroup is kept in LDS where that is
+ * estimated to be faster) with its block and run length, the right-hand sides
+ * split into 1, 2 or 4 chunks swept one after the other, at most 1, 2 or 3
+ * workgroups per CU or no limit,
  * two register budgets (the compiler's, and one that admits 4 wavefronts per
  * SIMD) and ordinary or non-temporal output stores -- on
  * scratch fields, and keeps the

@@ -1248,6 +1248,58 @@ bool staged_shape_f64(const Geom& g, const int T[4], int nrhs, StagedWalk& w, in
   return false;
 }
 
+// A shape that fits a workgroup can run either walk.  Blocks in LDS take up to
+// 512 threads to a workgroup where the open walk takes 256, stage links before
+// every slice, and their right-hand sides may need chunks: few workgroups, short
+// runs and many chunks are the open walk's.  Both were timed on shapes drawn
+// from lattices of 4 to 24 sites a side with 1 to 64 right-hand sides.
+
+// FP32: with two right-hand sides per thread 128 workgroups or fewer leave half
+// of the CUs idle; LDS / open was 0.81 to 1.35 there, 1.07 in the middle of 175
+// shapes, and 0.24 to 1.19 elsewhere, above 1.05 on 46 of 1208.
+bool f32_in_lds(const Geom& g, const int T[4], int nrhs, int R, int chunks, StagedWalk& w, int& links) {
+  return staged_shape(g, T, nrhs, R, chunks, 4, kStagedThreads, w, links) && (R == 1 || w.total_wg > 128);
+}
+
+// The hop and the FP64 operator: the lower of two estimated times.  In LDS:
+// rounds of workgroups, times the wavefronts per SIMD in one, times the slices,
+// times rows from outside the block and link words per thread; open: rounds of
+// wavefronts times slices; both with a share per row (one right-hand side of a
+// site), the open walk with one per site.  Fitted to the logarithms of the
+// times.  Of 4109 shapes of the hop 1977 took more than 1.05 times as long in
+// LDS, up to 2.06; of the 1490 kept there 46 do, up to 1.20.  FP64: 440 of
+// 2199, up to 1.70; of the 1599 kept there 45, up to 1.19.
+struct WalkFit {
+  double k[2], waves, run, halo, words, base, row;  // us; k by right-hand sides per thread
+  double open_k[2], open_waves, open_base, open_row, open_site;
+  int res, open_res;  // wavefronts per SIMD that run together
+};
+constexpr WalkFit kHopFit = {{2.09, 2.74}, 3.03, 0.905, 0.032, 0.094, 5.04, 29.4e-6, {7.34, 9.32}, 0.885, 10.6, 25.5e-6, 206e-6, 2, 3};
+constexpr WalkFit kF64Fit = {{0.394, 0.0}, 6.26, 0.563, 0.209, 0.077, 4.16, 101e-6, {3.63, 0.0}, 1.30, 2.84, 86.9e-6, 166e-6, 1, 1};
+
+// w.lds, w.Ts and w.total_wg are the launch's; words: 16-byte link words it stages; open_wg: the open walk's workgroups
+bool lds_is_faster(const Geom& g, const WalkFit& f, const StagedWalk& w, int R, int nrhs, long words, long open_wg) {
+  const int waves = w.threads / 64;
+  const long res = std::max<long>(1, std::min({160 * 1024L / w.lds, 4L * f.res / waves, (w.total_wg + 255) / 256}));
+  const double rounds = (double)((w.total_wg + 256 * res - 1) / (256 * res)), rows = (double)g.V * nrhs;
+  double halo = 0.0;
+  for (int m = 0; m < 3; ++m)
+    if (w.nb[m] > 1) halo += 2.0 / w.B[m];
+  const double in_lds = f.k[R - 1] * rounds * (res * waves / 4.0 + f.waves) * (w.Ts + f.run) * (1.0 + f.halo * halo) *
+                            (1.0 + f.words * words / w.threads) +
+                        f.base + f.row * rows;
+  const double per = (double)((open_wg + 255) / 256), together = std::min(per, (double)f.open_res);
+  const double open = f.open_k[R - 1] * per / together * (together + f.open_waves) * w.Ts + f.open_base +
+                      f.open_row * rows + f.open_site * g.V;
+  return in_lds < open;
+}
+
+bool f64_in_lds(const Geom& g, const int T[4], int nrhs, StagedWalk& w, int& links) {
+  WalkShape o;
+  return staged_shape_f64(g, T, nrhs, w, links) && walk_shape(g, T, nrhs, 1, 1, o) &&
+         lds_is_faster(g, kF64Fit, w, 1, nrhs, w.bs * 36L, o.total_wg);
+}
+
 template <int R, int LINKS, bool RES>
 hipError_t launch_staged_k(const Geom& g, const StagedWalk& w, const FineCfg& c, float kappa, const void* U,
                            const void* A, const void* in, void* out, int nrhs, hipStream_t s, const void* bres) {
@@ -1286,7 +1338,7 @@ hipError_t launch_walk_res(const Geom& g, const FineCfg& c, float kappa, const v
                            void* out, int nrhs, hipStream_t s, const void* bres) {
   StagedWalk w;
   int links = 0;
-  if (c.occ == 0 && staged_shape(g, c.T, nrhs, c.R, c.chunks, 4, kStagedThreads, w, links)) {
+  if (c.occ == 0 && f32_in_lds(g, c.T, nrhs, c.R, c.chunks, w, links)) {
     if (c.R == 2) return launch_staged<2, RES>(g, w, links, c, kappa, U, A, in, out, nrhs, s, bres);
     if (c.R == 1) return launch_staged<1, RES>(g, w, links, c, kappa, U, A, in, out, nrhs, s, bres);
   }
@@ -2017,6 +2069,12 @@ bool staged_eo_shape(const Geom& g, const int B[3], int Ts, int nrhs, int R, Sta
   return false;
 }
 
+bool eo_in_lds(const Geom& g, const int B[3], int Ts, int nrhs, int R, StagedWalk& w, int& links) {
+  WalkShape o;
+  return staged_eo_shape(g, B, Ts, nrhs, R, w, links) && eo_walk_shape(g, B, Ts, nrhs, R, o) &&
+         lds_is_faster(g, kHopFit, w, R, nrhs, w.bs * 36L, o.total_wg);
+}
+
 // M_ooee (or its inverse, given the inverse blocks): out = A in + coef add on
 // one parity (add may be null).
 // FULLIN: in is a full-lattice field (row = lattice site).
@@ -2192,7 +2250,7 @@ hipError_t launch_hop_eo_walk_k(const Geom& g, int parity, int nrhs, const EoWal
                                 hipStream_t s) {
   StagedWalk sw;
   int links = 0;
-  if (staged_eo_shape(g, ew.B, ew.Ts, nrhs, R, sw, links)) {
+  if (eo_in_lds(g, ew.B, ew.Ts, nrhs, R, sw, links)) {
     auto k = hop_eo_staged_kernel<R, 0, EPI, FULL2, ADDF, DOT>;
     if constexpr (R == 1) {
       if (links) k = hop_eo_staged_kernel<R, 1, EPI, FULL2, ADDF, DOT>;
@@ -2311,10 +2369,14 @@ double staged_cost(const StagedWalk& w, int R, bool f64) {
 double staged_walk_cost(const Geom& g, const int tile[4], int nrhs, int R, int chunks, bool f64) {
   StagedWalk w;
   int links = 0;
-  if (f64 ? !staged_shape_f64(g, tile, nrhs, w, links)
-          : !staged_shape(g, tile, nrhs, R, chunks, 4, kStagedThreads, w, links))
-    return -1.0;
+  if (f64 ? !f64_in_lds(g, tile, nrhs, w, links) : !f32_in_lds(g, tile, nrhs, R, chunks, w, links)) return -1.0;
   return staged_cost(w, R, f64);
+}
+
+double staged_eo_cost(const Geom& g, const int tile[4], int nrhs, int R) {
+  StagedWalk w;
+  int links = 0;
+  return eo_in_lds(g, tile, tile[3], nrhs, R, w, links) ? staged_cost(w, R, false) : -1.0;
 }
 
 std::vector<EoWalk> staged_eo_walks(const Geom& g, int nrhs, size_t count, double* cost) {
@@ -2326,17 +2388,15 @@ std::vector<EoWalk> staged_eo_walks(const Geom& g, int nrhs, size_t count, doubl
       for (int by = 1; g.L[0] % bx == 0 && by <= g.L[1] && bx * by <= smax; ++by)
         for (int bz = 1; g.L[1] % by == 0 && bz <= g.L[2] && bx * by * bz <= smax; ++bz)
           for (int ts = 1; g.L[2] % bz == 0 && ts <= g.L[3] / 2; ++ts) {
+            const int tile[4] = {bx, by, bz, ts};
+            const double us = (g.L[3] / 2) % ts == 0 ? staged_eo_cost(g, tile, nrhs, R) : -1.0;
+            if (us < 0.0) continue;
             EoWalk c;
             c.on = 1;
             c.R = R;
-            c.B[0] = bx;
-            c.B[1] = by;
-            c.B[2] = bz;
+            for (int m = 0; m < 3; ++m) c.B[m] = tile[m];
             c.Ts = ts;
-            StagedWalk w;
-            int links = 0;
-            if ((g.L[3] / 2) % ts == 0 && staged_eo_shape(g, c.B, ts, nrhs, R, w, links))
-              all.emplace_back(staged_cost(w, R, false), c);
+            all.emplace_back(us, c);
           }
   }
   std::stable_sort(all.begin(), all.end(), [](const auto& a, const auto& b) { return a.first < b.first; });
@@ -2438,7 +2498,7 @@ hipError_t launch_fine_f64(const Geom& g, int t_bc, int mode, double kappa, cons
     const int tile[4] = {fw->B[0], fw->B[1], fw->B[2], fw->Ts};
     StagedWalk sw;
     int links = 0;
-    if (fw->occ == 0 && staged_shape_f64(g, tile, nrhs, sw, links)) {
+    if (fw->occ == 0 && f64_in_lds(g, tile, nrhs, sw, links)) {
       auto k = links == 2 ? fine_walk_f64_kernel<2> : links == 1 ? fine_walk_f64_kernel<1> : fine_walk_f64_kernel<0>;
       hipLaunchKernelGGL(k, dim3((unsigned)(sw.per * 8)), dim3((unsigned)sw.threads), sw.lds, s, g, nrhs, kappa,
                          static_cast<const cplx<double>*>(U), static_cast<const double*>(A),

@@ -12,6 +12,7 @@ import pytest
 import oracle as O
 from oracle import evenodd as EO
 import synth
+from test_walk_shapes_host import EO_LDS
 
 pytestmark = pytest.mark.gpu
 
@@ -293,6 +294,30 @@ def test_hop_eo_walk_with_its_block_in_lds(lat, nrhs, walk, R):
     for a, b in zip(*out):
         assert torch.equal(a, b)
     ctx.set_eo_walk(nrhs, None)
+
+
+@pytest.mark.parametrize("dims,nrhs,R,walk", EO_LDS)
+def test_hop_eo_shapes_kept_in_lds(gpu_lib, dims, nrhs, R, walk):
+    """Shapes that the rule keeps in LDS: the tiled kernel's fields bit for bit,
+    both parities and the Schur launches."""
+    import torch
+
+    ctx = gpu_lib.Context(dims, t_bc=-1)
+    ctx.set_gauge(synth.gauge_haar(dims, 4200))
+    ctx.build_clover(CSW, KAPPA)
+    chi = dev(EO.to_cb(synth.spinor_source(dims, nrhs, 4201, np.complex64), dims, 0))
+    out = []
+    for tile in (None, walk):
+        ctx.set_eo_walk(nrhs, tile, R if tile else 0)
+        o = [torch.empty_like(chi) for _ in range(3)]
+        for p in (0, 1):
+            ctx.hop_eo(o[p], chi, p)
+        ctx.schur(o[2], chi)
+        out.append(o)
+    torch.cuda.synchronize()
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+    ctx.close()
 
 
 @pytest.mark.parametrize("dims", [(8, 8, 8, 8), (4, 6, 10, 4), (2, 2, 2, 4), (12, 4, 8, 16)])

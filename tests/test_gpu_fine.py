@@ -14,6 +14,7 @@ import pytest
 
 import oracle as O
 import synth
+from test_walk_shapes_host import F64_LDS, FINE_LDS
 
 pytestmark = pytest.mark.gpu
 
@@ -438,6 +439,26 @@ def test_walk_with_its_block_in_lds(gpu_lib, tmp_path, dims, n, R, tile, nt, chu
     torch.cuda.synchronize()
     assert torch.equal(z, z0)
     assert rel_l2(z.cpu().numpy(), O.dwc(U, A, KAPPA, psi.astype(np.complex128), dims)) < 1e-12
+
+
+@pytest.mark.parametrize("dims,n,R,tile,nt,chunks", FINE_LDS + F64_LDS)
+def test_shapes_kept_in_lds(gpu_lib, tmp_path, dims, n, R, tile, nt, chunks):
+    """Shapes that the rule keeps in LDS, at the edges of what it takes: bit for
+    bit the tiled kernel, in FP32 and FP64."""
+    import torch
+
+    ctx = _ctx(gpu_lib, dims, synth.gauge_haar(dims, 1801))
+    x = _dev(torch, synth.spinor_source(dims, n, 1802, np.complex64))
+    out = []
+    for i, (r, t, curve, c) in enumerate(((1, (1, 1, 1, 1), 0, 1), (R, tile, 2, chunks))):
+        _set_walk(torch, ctx, dims, tmp_path / f"w{i}.txt", n, r, t, curve, nt, c)
+        ctx.set_f64_walk(n, tile if curve == 2 else None, nt)
+        out.append([torch.empty_like(x), torch.empty_like(x, dtype=torch.complex128)])
+        ctx.dwc(out[i][0], x)
+        ctx.dwc(out[i][1], x.to(torch.complex128))
+    torch.cuda.synchronize()
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
 
 
 @pytest.mark.parametrize("dims", [(8, 8, 8, 8), (5, 3, 9, 4), (6, 10, 4, 6), (2, 2, 2, 2), (7, 7, 7, 11), (16, 2, 4, 6)])

@@ -15,6 +15,7 @@ import pytest
 
 import oracle as O
 import synth
+from test_walk_shapes_host import EO_LDS_SMOOTHER, FINE_LDS_RESIDUAL
 
 pytestmark = pytest.mark.gpu
 
@@ -314,6 +315,27 @@ def test_even_odd_smoother_with_the_block_in_lds(gpu_lib, nrhs, tile, R):
     ctx, mg = build(gpu_lib, dims, U, [(4, 4, 4, 4)], [16], setup_iters=1, smooth_steps=4)
     ctx.set_eo_walk(nrhs, tile, R)
     v = synth.spinor_source(dims, nrhs, 9301, np.complex64)
+    z = torch.empty(v.shape, dtype=torch.complex64, device="cuda")
+    mg.precondition(z, dev(v), nu_pre=0, nu_post=3, coarsest_iters=0, coarse_prec="bf16", fine_eo=True)
+    want = _eo_smoother_ref(U, A, KAPPA, v, dims, 3)
+    got = z.cpu().numpy()
+    for k in range(nrhs):
+        assert np.linalg.norm(got[:, :, k] - want[:, :, k]) < 1e-5 * np.linalg.norm(want[:, :, k]), k
+    mg.close()
+    ctx.close()
+
+
+@pytest.mark.parametrize("dims,nrhs,R,tile", EO_LDS_SMOOTHER)
+def test_even_odd_smoother_shapes_kept_in_lds(gpu_lib, dims, nrhs, R, tile):
+    """As test_even_odd_smoother_with_the_block_in_lds, with shapes that the rule
+    keeps there: 1e-5 per column against the smoother in double precision."""
+    import torch
+
+    U = synth.gauge_haar(dims, 4242)
+    A = O.clover_packed(U, dims, CSW, KAPPA)
+    ctx, mg = build(gpu_lib, dims, U, [(4, 4, 4, 4)], [16], setup_iters=1, smooth_steps=4)
+    ctx.set_eo_walk(nrhs, tile, R)
+    v = synth.spinor_source(dims, nrhs, 9302, np.complex64)
     z = torch.empty(v.shape, dtype=torch.complex64, device="cuda")
     mg.precondition(z, dev(v), nu_pre=0, nu_post=3, coarsest_iters=0, coarse_prec="bf16", fine_eo=True)
     want = _eo_smoother_ref(U, A, KAPPA, v, dims, 3)
@@ -652,6 +674,13 @@ def test_vcycle_same_with_the_block_in_lds(small, tmp_path, n, R, tile, nt):
         z.append(torch.empty_like(v))
         mg.precondition(z[-1], v, nu_pre=1, nu_post=2, coarsest_iters=8, coarse_prec="bf16", fine_eo=False)
     assert torch.equal(z[0], z[1])
+
+
+@pytest.mark.parametrize("n,R,tile,nt", FINE_LDS_RESIDUAL)
+def test_vcycle_same_with_shapes_kept_in_lds(small, tmp_path, n, R, tile, nt):
+    """As test_vcycle_same_with_the_block_in_lds, with shapes of two right-hand
+    sides per thread that the rule keeps there."""
+    test_vcycle_same_with_the_block_in_lds(small, tmp_path, n, R, tile, nt)
 
 
 def test_solve_same_with_f64_walk(small):

@@ -1,0 +1,116 @@
+"""Which walk a launch shape runs: the rules of csrc/fine.hip, called in the
+built library (host code only).  A shape whose block fits a workgroup keeps it
+in LDS unless the walk without is expected to be faster."""
+
+import ctypes as C
+
+import pytest
+
+from paper_2211_13719_amd._lib import lib
+
+
+class Geom(C.Structure):
+    _fields_ = [("L", C.c_int * 4), ("V", C.c_int), ("stride", C.c_int * 4), ("T", C.c_int * 4),
+                ("order", C.c_void_p), ("nbr", C.c_void_p)]
+
+
+def geom(dims):
+    g = Geom()
+    step = 1
+    for m in range(4):
+        g.L[m], g.stride[m] = dims[m], step
+        step *= dims[m]
+    g.V = step
+    return g
+
+
+def _fn(name, res, *args):
+    f = lib[name]
+    f.restype, f.argtypes = res, args
+    return f
+
+
+_walk_cost = _fn("_ZN4mrhs16staged_walk_costERKNS_4GeomEPKiiiib", C.c_double, C.POINTER(Geom), C.POINTER(C.c_int),
+                 C.c_int, C.c_int, C.c_int, C.c_bool)
+_eo_cost = _fn("_ZN4mrhs14staged_eo_costERKNS_4GeomEPKiii", C.c_double, C.POINTER(Geom), C.POINTER(C.c_int), C.c_int,
+               C.c_int)
+
+
+def fine_in_lds(dims, n, R, tile, chunks=1):
+    return _walk_cost(C.byref(geom(dims)), (C.c_int * 4)(*tile), n, R, chunks, False) >= 0
+
+
+def f64_in_lds(dims, n, tile):
+    return _walk_cost(C.byref(geom(dims)), (C.c_int * 4)(*tile), n, 1, 1, True) >= 0
+
+
+def eo_in_lds(dims, n, R, tile):
+    return _eo_cost(C.byref(geom(dims)), (C.c_int * 4)(*tile), n, R) >= 0
+
+
+# Shapes that keep their block in LDS, at the edges of what it takes; the GPU
+# tests run them: (lattice, Nrhs, right-hand sides per thread, tile, ...)
+FINE_LDS = [  # ..., non-temporal stores, chunks
+    ((6, 10, 4, 40), 12, 2, (3, 5, 4, 1), 0, 1),  # a block that spans z; 360 of 384 threads
+    ((6, 10, 4, 12), 24, 2, (2, 2, 2, 4), 1, 2),  # two chunks, runs of four slices
+    ((8, 12, 8, 6), 24, 2, (2, 2, 2, 6), 0, 2),   # one run over the whole t extent
+    ((6, 10, 4, 12), 64, 2, (2, 2, 4, 1), 1, 1),  # 512 threads, runs of one slice
+]
+F64_LDS = [
+    ((6, 10, 4, 12), 12, 1, (3, 5, 4, 3), 0, 1),  # three chunks, 240 of 256 threads
+    ((6, 10, 4, 12), 64, 1, (2, 2, 2, 12), 1, 1),  # two chunks, the whole t extent
+]
+FINE_LDS_RESIDUAL = [(12, 2, (2, 2, 2, 2), 0), (16, 2, (2, 4, 2, 1), 1)]  # on 8^4
+EO_LDS = [
+    ((8, 12, 8, 8), 48, 2, (2, 3, 4, 1)),   # two chunks, 288 of 320 threads, runs of one output site
+    ((8, 12, 8, 8), 24, 2, (2, 4, 2, 4)),   # one run over the whole t extent
+    ((8, 12, 8, 8), 6, 1, (2, 3, 4, 4)),    # more than three link words per thread, 144 of 192 threads
+    ((8, 12, 8, 8), 13, 1, (4, 3, 2, 4)),
+    ((8, 12, 8, 8), 24, 1, (2, 2, 8, 1)),   # a block that spans z, two chunks
+    ((6, 12, 10, 16), 48, 1, (2, 4, 5, 4)),  # four chunks
+    ((6, 12, 10, 16), 32, 2, (2, 2, 5, 2)),
+]
+EO_LDS_SMOOTHER = [((8, 8, 8, 8), 24, 2, (2, 4, 2, 4)), ((8, 12, 8, 8), 48, 2, (2, 3, 4, 1)),
+                   ((8, 8, 8, 8), 6, 1, (4, 2, 2, 2)), ((8, 8, 8, 8), 48, 1, (2, 8, 2, 1))]
+
+
+def test_shapes_of_the_lds_tests_run_there():
+    for dims, n, R, tile, _, chunks in FINE_LDS:
+        assert fine_in_lds(dims, n, R, tile, chunks), (dims, n)
+    for dims, n, _, tile, _, _ in F64_LDS:
+        assert f64_in_lds(dims, n, tile), (dims, n)
+    for n, R, tile, _ in FINE_LDS_RESIDUAL:
+        assert fine_in_lds((8, 8, 8, 8), n, R, tile), n
+    for dims, n, R, tile in EO_LDS + EO_LDS_SMOOTHER:
+        assert eo_in_lds(dims, n, R, tile), (dims, n)
+
+
+@pytest.mark.parametrize("kind,dims,n,R,tile", [
+    # (open, LDS) in us
+    ("f32", (8, 8, 8, 8), 12, 2, (4, 4, 4, 1)),         # 13.3, 17.3
+    ("f32", (16, 8, 8, 16), 12, 2, (4, 4, 4, 2)),       # 26.9, 30.9
+    ("eo", (8, 8, 8, 8), 16, 1, (4, 4, 4, 1)),          # 25.0, 38.9
+    ("eo", (16, 16, 16, 16), 24, 1, (4, 4, 4, 1)),      # 174, 293
+    ("eo", (24, 24, 24, 24), 24, 1, (4, 4, 4, 3)),      # 1031, 1263
+    ("f64", (8, 8, 8, 8), 12, 1, (4, 4, 4, 1)),         # 17.2, 19.8
+    ("f64", (18, 4, 16, 8), 24, 1, (6, 4, 2, 4)),       # 47.6, 78.1
+])
+def test_shapes_faster_without_lds_stay_out(kind, dims, n, R, tile):
+    """A stored or hand-set shape whose block fits LDS but was measured slower
+    there runs the walk it was chosen for."""
+    got = {"f32": lambda: fine_in_lds(dims, n, R, tile), "f64": lambda: f64_in_lds(dims, n, tile),
+           "eo": lambda: eo_in_lds(dims, n, R, tile)}[kind]()
+    assert not got
+
+
+@pytest.mark.parametrize("kind,dims,n,R,tile", [
+    ("f32", (24, 24, 24, 24), 12, 2, (3, 3, 8, 6)),     # 427, 320
+    ("f32", (16, 16, 16, 32), 6, 1, (4, 4, 4, 4)),      # 129, 78
+    ("eo", (24, 24, 24, 24), 6, 1, (4, 4, 4, 12)),      # 435, 287
+    ("eo", (24, 24, 24, 24), 64, 2, (2, 3, 4, 6)),      # 1932, 1770
+    ("f64", (16, 16, 16, 32), 4, 1, (4, 4, 4, 32)),     # 467, 313
+])
+def test_shapes_faster_in_lds_run_there(kind, dims, n, R, tile):
+    got = {"f32": lambda: fine_in_lds(dims, n, R, tile), "f64": lambda: f64_in_lds(dims, n, tile),
+           "eo": lambda: eo_in_lds(dims, n, R, tile)}[kind]()
+    assert got
