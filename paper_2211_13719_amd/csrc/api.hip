@@ -500,7 +500,7 @@ mrhs_status mrhs_hop_eo_apply(mrhs_ctx ctx, void* out, const void* in, int32_t n
   MRHS_HIP(ctx, launch_hop_eo(p64, ctx->g.V / 2, static_cast<const int4*>(ctx->eo_tab[out_parity].p),
                               static_cast<const int*>(ctx->eo_order[out_parity].p), p64 ? ctx->U64.p : ctx->U32.p,
                               in, out, nrhs, ctx->stream, 0, nullptr, nullptr, 0.0, &ctx->g, out_parity,
-                              eo_config(ctx, nrhs)));
+                              p64 ? nullptr : eo_config(ctx, nrhs)));
   return MRHS_OK;
 }
 
@@ -612,10 +612,11 @@ mrhs_status mrhs_schur_apply(mrhs_ctx ctx, void* out, const void* in, int32_t nr
   // t2 = A_o^-1 (H_oe in), out = A_e in - kappa^2 (H_eo t2): two fused launches
   const auto* oe = static_cast<const int*>(ctx->eo_order[0].p);
   const auto* oo = static_cast<const int*>(ctx->eo_order[1].p);
+  const EoWalk* ew = p64 ? nullptr : eo_config(ctx, nrhs);  // the walk is FP32
   MRHS_HIP(ctx, launch_hop_eo(p64, nh, to, oo, U, in, t2, nrhs, ctx->stream, 1, p64 ? ctx->Ainv64.p : ctx->Ainv32.p,
-                              nullptr, 0.0, &ctx->g, 1, eo_config(ctx, nrhs)));
+                              nullptr, 0.0, &ctx->g, 1, ew));
   MRHS_HIP(ctx, launch_hop_eo(p64, nh, te, oe, U, t2, out, nrhs, ctx->stream, 2, p64 ? ctx->A64.p : ctx->A32.p, in,
-                              -ctx->kappa * ctx->kappa, &ctx->g, 0, eo_config(ctx, nrhs)));
+                              -ctx->kappa * ctx->kappa, &ctx->g, 0, ew));
   return MRHS_OK;
 }
 

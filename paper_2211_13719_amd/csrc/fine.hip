@@ -2366,6 +2366,17 @@ double staged_cost(const StagedWalk& w, int R, bool f64) {
          (R == 2 ? 1.0 : 0.65);
 }
 
+// Less than staged_cost of any run length: every round full and no slice read
+// twice.  slices: those of all blocks and chunks.
+double staged_cost_bound(const StagedWalk& w, int R, long slices) {
+  const int waves = w.threads / 64;
+  const double res = (double)std::max<long>(1, std::min(160 * 1024L / w.lds, 8L / waves));
+  double halo = 0.0;
+  for (int m = 0; m < 3; ++m)
+    if (w.nb[m] > 1) halo += 2.0 / w.B[m];
+  return slices / 256.0 * (waves / 4.0 + 0.75 / res) * (1.0 + 0.05 * halo) * (1.0 + 2.0 / w.nc) * (R == 2 ? 1.0 : 0.65);
+}
+
 double staged_walk_cost(const Geom& g, const int tile[4], int nrhs, int R, int chunks, bool f64) {
   StagedWalk w;
   int links = 0;
@@ -2379,7 +2390,7 @@ double staged_eo_cost(const Geom& g, const int tile[4], int nrhs, int R) {
   return eo_in_lds(g, tile, tile[3], nrhs, R, w, links) ? staged_cost(w, R, false) : -1.0;
 }
 
-std::vector<EoWalk> staged_eo_walks(const Geom& g, int nrhs, size_t count, double* cost) {
+std::vector<EoWalk> staged_eo_walks(const Geom& g, int nrhs, size_t count) {
   std::vector<std::pair<double, EoWalk>> all;
   for (int R = 1; R <= 2; ++R) {
     if (nrhs % R) continue;
@@ -2389,34 +2400,20 @@ std::vector<EoWalk> staged_eo_walks(const Geom& g, int nrhs, size_t count, doubl
         for (int bz = 1; g.L[1] % by == 0 && bz <= g.L[2] && bx * by * bz <= smax; ++bz)
           for (int ts = 1; g.L[2] % bz == 0 && ts <= g.L[3] / 2; ++ts) {
             const int tile[4] = {bx, by, bz, ts};
-            const double us = (g.L[3] / 2) % ts == 0 ? staged_eo_cost(g, tile, nrhs, R) : -1.0;
-            if (us < 0.0) continue;
+            const double cost = (g.L[3] / 2) % ts == 0 ? staged_eo_cost(g, tile, nrhs, R) : -1.0;
+            if (cost < 0.0) continue;
             EoWalk c;
             c.on = 1;
             c.R = R;
             for (int m = 0; m < 3; ++m) c.B[m] = tile[m];
             c.Ts = ts;
-            all.emplace_back(us, c);
+            all.emplace_back(cost, c);
           }
   }
   std::stable_sort(all.begin(), all.end(), [](const auto& a, const auto& b) { return a.first < b.first; });
-  if (cost && !all.empty()) *cost = all[0].first;
   std::vector<EoWalk> out;
   for (size_t i = 0; i < all.size() && i < count; ++i) out.push_back(all[i].second);
   return out;
-}
-
-// The first of them on fields beyond the caches (2^20 rows of one right-hand
-// side: 48 MiB of each checkerboard field) unless the lattice's divisors cut it
-// badly (estimate per site).  Of 260 drawn lattices and batches the first
-// against the tiled kernel took 0.73 to 0.96 of the time there, and 0.8 to 1.5
-// on smaller fields, whose rows the tiled kernel finds in the caches.
-EoWalk eo_default(const Geom& g, int nrhs) {
-  const double rows = (double)g.V * nrhs;
-  if (rows < 1 << 20) return EoWalk{};
-  double cost = 0.0;
-  const std::vector<EoWalk> w = staged_eo_walks(g, nrhs, 1, &cost);
-  return !w.empty() && cost < 1.55e-5 * rows ? w[0] : EoWalk{};
 }
 
 // Every staged walk of the lattice, as f(tile, R, chunks, cost).
@@ -2454,36 +2451,107 @@ std::vector<FineCfg> staged_walks(const Geom& g, int nrhs, bool f64, size_t coun
   return out;
 }
 
-FineCfg fine_default(const Geom& g, int nrhs) {
+// Ascending divisors of n up to most.
+struct Divisors {
+  int d[1536], count = 0;  // no number below 2^31 has more
+  Divisors(int n, long most) {
+    for (int i = 1; (long)i * i <= n && i <= most; ++i)
+      if (n % i == 0) d[count++] = i;
+    for (int i = count - 1; i >= 0; --i)
+      if (n / d[i] > d[i] && n / d[i] <= most) d[count++] = n / d[i];
+  }
+};
+
+// The walk in LDS of the least estimated time below `limit`, the first of
+// equal ones; false if there is none.  Called by the first apply of a batch
+// size, so it allocates nothing and leaves out what cannot win: a block whose
+// time is at least the best so far even with whole rounds and one long run.
+// 24^4 at 12 right-hand sides 18 us for the operator and 31 for the hop (every
+// shape costed and the hop's sorted: 107 and 218), 8^4 at 12 4.6 (9.7).
+// HOP: walks of the checkerboard hop, best.T[3] in output sites.
+template <bool HOP>
+bool best_staged_walk(const Geom& g, int nrhs, double limit, FineCfg& best) {
+  const Divisors dx(g.L[0], kStagedThreads * 4), dy(g.L[1], kStagedThreads * 4), dz(g.L[2], kStagedThreads * 4),
+      dt(HOP ? g.L[3] / 2 : g.L[3], g.L[3]);
+  bool found = false;
+  for (int R = 1; R <= 2; ++R) {
+    if (nrhs % R) continue;
+    // the hop's chunks are the fewest that fit its block
+    for (int chunks = 1; chunks <= (HOP ? 1 : 4); chunks *= 2) {
+      if (nrhs % chunks || (nrhs / chunks) % R) continue;
+      const int smax = HOP ? kStagedThreads * 4 * R / nrhs : kStagedThreads / (nrhs / chunks / R);
+      for (int ix = 0; ix < dx.count && dx.d[ix] <= smax; ++ix)
+        for (int iy = 0; iy < dy.count && dx.d[ix] * dy.d[iy] <= smax; ++iy)
+          for (int iz = 0; iz < dz.count && (long)dx.d[ix] * dy.d[iy] * dz.d[iz] <= smax; ++iz) {
+            const int T[4] = {dx.d[ix], dy.d[iy], dz.d[iz], dt.d[dt.count - 1]};
+            StagedWalk w;
+            int links = 0;
+            if (HOP ? !staged_eo_shape(g, T, T[3], nrhs, R, w, links)
+                    : !staged_shape(g, T, nrhs, R, chunks, 4, kStagedThreads, w, links))
+              continue;
+            const long slices = (long)w.nchunk * w.nblk * T[3];
+            if (staged_cost_bound(w, R, slices) >= limit) continue;
+            for (int it = 0; it < dt.count; ++it) {
+              w.Ts = dt.d[it];
+              w.total_wg = slices / w.Ts;
+              const double cost = staged_cost(w, R, false);
+              if (cost >= limit) continue;
+              const int Ti[4] = {T[0], T[1], T[2], w.Ts};
+              if (HOP ? !eo_in_lds(g, Ti, Ti[3], nrhs, R, w, links) : !f32_in_lds(g, Ti, nrhs, R, chunks, w, links)) continue;
+              found = true;
+              limit = cost;
+              best.walk = 1;
+              best.R = R;
+              best.chunks = chunks;
+              for (int m = 0; m < 4; ++m) best.T[m] = Ti[m];
+            }
+          }
+    }
+  }
+  return found;
+}
+
+// The best of its walks on fields beyond the caches (2^20 rows of one right-hand
+// side: 48 MiB of each checkerboard field) unless the lattice's divisors cut it
+// badly (estimate per site).  Of 260 drawn lattices and batches the first
+// against the tiled kernel took 0.73 to 0.96 of the time there, and 0.8 to 1.5
+// on smaller fields, whose rows the tiled kernel finds in the caches.
+EoWalk eo_default(const Geom& g, int nrhs) {
+  EoWalk out;
   FineCfg best;
-  double cost = 0.0;
-  each_staged_walk(g, nrhs, false, [&](const int* tile, int R, int chunks, double c) {
-    if (best.R && c >= cost) return;
-    cost = c;
-    best.walk = 1;
-    best.R = R;
-    best.chunks = chunks;
-    for (int m = 0; m < 4; ++m) best.T[m] = tile[m];
-  });
-  // Against the tiled kernel, on 260 drawn lattices and batches without tuning:
-  // even batches below 8 took 0.44 to 1.05 of its time, fields of 3e5 rows and
-  // more of one right-hand side 0.57 to 1.06.  On smaller fields, whose rows the
-  // tiled kernel finds in the caches, and for odd batches it took up to 1.3 where
-  // the lattice's divisors cut it badly: there both times are estimated (fits
-  // to the same draws, microseconds) and a lead is asked for.  One right-hand
-  // side: 1.04 on average up to 5e4 sites, 0.97 at 16^3 x 32 and 0.54 at 24^4.
-  const double V = g.V, rows = V * nrhs, staged = 3.8 * cost - 0.5;
-  bool take = true;
-  if (nrhs == 1)
-    take = g.V >= 1 << 17;
-  else if (nrhs % 2)
-    take = staged < 0.9 * (6.6 + 96.4e-6 * rows + 159e-6 * V);
-  else if (nrhs >= 8 && rows < 3e5)
-    take = staged < 0.75 * (9.0 + 62.7e-6 * rows + 358e-6 * V);
-  if (!take) return FineCfg{};
+  const double rows = (double)g.V * nrhs;
+  for (int m = 0; m < 4; ++m)
+    if (g.L[m] % 2) return out;
+  if (rows < 1 << 20 || !best_staged_walk<true>(g, nrhs, 1.55e-5 * rows, best)) return out;
+  out.on = 1;
+  out.R = best.R;
+  for (int m = 0; m < 3; ++m) out.B[m] = best.T[m];
+  out.Ts = best.T[3];
+  return out;
+}
+
+// Against the tiled kernel, on 260 drawn lattices and batches without tuning:
+// even batches below 8 took 0.44 to 1.05 of its time, fields of 3e5 rows and
+// more of one right-hand side 0.57 to 1.06.  On smaller fields, whose rows the
+// tiled kernel finds in the caches, and for odd batches it took up to 1.3 where
+// the lattice's divisors cut it badly: there both times are estimated (fits
+// to the same draws, microseconds) and a lead is asked for.  One right-hand
+// side: 1.04 on average up to 5e4 sites, 0.97 at 16^3 x 32 and 0.54 at 24^4.
+FineCfg fine_default(const Geom& g, int nrhs) {
+  const double V = g.V, rows = V * nrhs;
+  double us = 1e30;  // what the walk has to beat; it takes 3.8 cost - 0.5
+  if (nrhs == 1) {
+    if (g.V < 1 << 17) return FineCfg{};
+  } else if (nrhs % 2) {
+    us = 0.9 * (6.6 + 96.4e-6 * rows + 159e-6 * V);
+  } else if (nrhs >= 8 && rows < 3e5) {
+    us = 0.75 * (9.0 + 62.7e-6 * rows + 358e-6 * V);
+  }
+  FineCfg best;
+  if (!best_staged_walk<false>(g, nrhs, (us + 0.5) / 3.8, best)) return FineCfg{};
   // chunks of 16 and more write whole 128-byte lines, which need not stay in
   // the cache; non-temporal stores of less than a line cost up to a tenth
-  best.nt = best.R && nrhs / best.chunks >= 16;
+  best.nt = nrhs / best.chunks >= 16;
   return best;
 }
 

@@ -219,7 +219,7 @@ double staged_walk_cost(const Geom& g, const int tile[4], int nrhs, int R, int c
 std::vector<FineCfg> staged_walks(const Geom& g, int nrhs, bool f64, size_t count);
 // and of the checkerboard hop's walks that do (FP32), Ts in output sites
 double staged_eo_cost(const Geom& g, const int tile[4], int nrhs, int R);
-std::vector<EoWalk> staged_eo_walks(const Geom& g, int nrhs, size_t count, double* cost = nullptr);
+std::vector<EoWalk> staged_eo_walks(const Geom& g, int nrhs, size_t count);
 // the untuned checkerboard hop (FP32)
 EoWalk eo_default(const Geom& g, int nrhs);
 // the untuned FP32 operator A - kappa H: the best of them, or R = 0 for the

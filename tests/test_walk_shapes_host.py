@@ -114,3 +114,87 @@ def test_shapes_faster_in_lds_run_there(kind, dims, n, R, tile):
     got = {"f32": lambda: fine_in_lds(dims, n, R, tile), "f64": lambda: f64_in_lds(dims, n, tile),
            "eo": lambda: eo_in_lds(dims, n, R, tile)}[kind]()
     assert got
+
+
+class FineCfg(C.Structure):
+    _fields_ = [("R", C.c_int), ("T", C.c_int * 4), ("curve", C.c_int), ("walk", C.c_int), ("occ", C.c_int),
+                ("nt", C.c_int), ("chunks", C.c_int), ("cap", C.c_int), ("lds", C.c_uint), ("order", C.c_void_p),
+                ("us", C.c_float)]
+
+
+class EoWalk(C.Structure):
+    _fields_ = [("on", C.c_int), ("R", C.c_int), ("B", C.c_int * 3), ("Ts", C.c_int), ("us", C.c_float),
+                ("us_tiled", C.c_float)]
+
+
+_fine_default = _fn("_ZN4mrhs12fine_defaultERKNS_4GeomEi", FineCfg, C.POINTER(Geom), C.c_int)
+_eo_default = _fn("_ZN4mrhs10eo_defaultERKNS_4GeomEi", EoWalk, C.POINTER(Geom), C.c_int)
+
+
+def fine_default(dims, n):
+    """(R, tile, chunks) of the untuned operator, None for the tiled kernel."""
+    c = _fine_default(C.byref(geom(dims)), n)
+    return (c.R, tuple(c.T), c.chunks) if c.R else None
+
+
+def eo_default(dims, n):
+    """(R, tile) of the untuned checkerboard hop, None for the tiled kernel."""
+    c = _eo_default(C.byref(geom(dims)), n)
+    return (c.R, (*c.B, c.Ts)) if c.on else None
+
+
+def _divisors(n):
+    return [d for d in range(1, n + 1) if n % d == 0]
+
+
+def _tiles(dims, lt, smax):
+    return [(x, y, z, t) for x in _divisors(dims[0]) for y in _divisors(dims[1]) for z in _divisors(dims[2])
+            if x * y * z <= smax for t in _divisors(lt)]
+
+
+@pytest.mark.parametrize("dims", [(4, 4, 4, 4), (5, 3, 9, 4), (12, 10, 6, 14), (16, 16, 16, 32), (7, 7, 7, 11),
+                                  (24, 24, 24, 24)])
+def test_untuned_choice_is_that_of_the_full_search(dims):
+    """The pruned search of the first apply finds what costing every shape does."""
+    g = geom(dims)
+    V = g.V
+    for n in (1, 2, 3, 6, 7, 12, 24, 64):
+        rows = V * n
+        best, cost = None, 1e30
+        for R in (1, 2):
+            for chunks in (1, 2, 4):
+                if n % chunks or (n // chunks) % R:
+                    continue
+                for T in _tiles(dims, dims[3], 512 * R * chunks // n):
+                    c = _walk_cost(C.byref(g), (C.c_int * 4)(*T), n, R, chunks, False)
+                    if 0 <= c < cost:
+                        best, cost = (R, T, chunks), c
+        us = 3.8 * cost - 0.5
+        if ((n == 1 and V < 1 << 17) or (n > 1 and n % 2 and us >= 0.9 * (6.6 + 96.4e-6 * rows + 159e-6 * V))
+                or (n % 2 == 0 and n >= 8 and rows < 3e5 and us >= 0.75 * (9.0 + 62.7e-6 * rows + 358e-6 * V))):
+            best = None
+        assert fine_default(dims, n) == best, n
+        best, cost = None, 1.55e-5 * rows
+        if all(L % 2 == 0 for L in dims) and rows >= 1 << 20:
+            for R in (1, 2):
+                for T in _tiles(dims, dims[3] // 2, 2048 * R // n) if n % R == 0 else []:
+                    c = _eo_cost(C.byref(g), (C.c_int * 4)(*T), n, R)
+                    if 0 <= c < cost:
+                        best, cost = (R, T), c
+        assert eo_default(dims, n) == best, n
+
+
+def test_untuned_choice_costs_less_than_a_tenth_of_a_launch():
+    """The first apply of a batch size makes the choice on the host: on
+    24^3 x 128 at 12 right-hand sides in less than a tenth of the launch's
+    1530 us (operator) and 1000 us (hop)."""
+    import time
+
+    g = geom((24, 24, 24, 128))
+    for f, us in ((_fine_default, 153), (_eo_default, 100)):
+        best = 1e9
+        for _ in range(20):
+            t = time.perf_counter()
+            f(C.byref(g), 12)
+            best = min(best, time.perf_counter() - t)
+        assert best * 1e6 < us
