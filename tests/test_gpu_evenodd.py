@@ -12,7 +12,7 @@ import pytest
 import oracle as O
 from oracle import evenodd as EO
 import synth
-from test_walk_shapes_host import EO_LDS
+from test_walk_shapes_host import EO_LDS, UNTUNED_EO
 
 pytestmark = pytest.mark.gpu
 
@@ -363,4 +363,35 @@ def test_tune_chooses_a_checkerboard_kernel(gpu_lib):
         assert ut > 0 and us > 0 and us <= ut * 1.0001
         if on:
             assert all(d % b == 0 for d, b in zip(dims[:3], tile[:3])) and (dims[3] // 2) % tile[3] == 0
+    ctx.close()
+
+
+@pytest.mark.parametrize("dims,n,choice", UNTUNED_EO)
+def test_untuned_hop_eo_choice_is_the_tiled_result(gpu_lib, dims, n, choice):
+    """The walk that an untuned context picks for the checkerboard hop of a large
+    field, and the tiled kernel of a small one: the choice as reported, both
+    parities and the Schur launches bit for bit the tiled kernel's."""
+    import torch
+
+    V = int(np.prod(dims))
+    g = torch.Generator(device="cuda").manual_seed(4300)
+    ctx = gpu_lib.Context(dims, t_bc=-1)
+    ctx.set_gauge(torch.view_as_complex(0.1 * torch.randn(V, 4, 3, 3, 2, generator=g, device="cuda", dtype=torch.float64)))
+    ctx.build_clover(CSW, KAPPA)
+    chi = torch.view_as_complex(torch.randn(V // 2, 12, n, 2, generator=g, device="cuda"))
+    out = []
+    for tiled in (False, True):
+        if tiled:
+            ctx.set_eo_walk(n, None)
+        on, R, tile, us, us_tiled = ctx.get_eo_walk(n)
+        assert (on, us, us_tiled) == (choice is not None and not tiled, 0, 0)
+        assert not on or (R, tile) == choice
+        o = [torch.empty_like(chi) for _ in range(3)]
+        for p in (0, 1):
+            ctx.hop_eo(o[p], chi, p)
+        ctx.schur(o[2], chi)
+        out.append(o)
+    torch.cuda.synchronize()
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
     ctx.close()

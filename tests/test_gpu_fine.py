@@ -14,7 +14,7 @@ import pytest
 
 import oracle as O
 import synth
-from test_walk_shapes_host import F64_LDS, FINE_LDS
+from test_walk_shapes_host import F64_LDS, FINE_LDS, UNTUNED_FINE, fine_default
 
 pytestmark = pytest.mark.gpu
 
@@ -478,3 +478,28 @@ def test_untuned_launch_is_the_tiled_result(gpu_lib, tmp_path, dims):
         ctx.dwc(y0, x)
         torch.cuda.synchronize()
         assert torch.equal(y, y0), n
+
+
+def _random_gauge(torch, V, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    return torch.view_as_complex(0.4 * torch.randn(V, 4, 3, 3, 2, generator=g, device="cuda", dtype=torch.float64))
+
+
+@pytest.mark.parametrize("dims,n,choice", UNTUNED_FINE)
+def test_untuned_choice_is_the_tiled_result(gpu_lib, tmp_path, dims, n, choice):
+    """Each kind of untuned launch -- the host tests say which one it is -- gives
+    the tiled kernel's bits."""
+    import torch
+
+    assert fine_default(dims, n) == choice
+    V = int(np.prod(dims))
+    ctx = _ctx(gpu_lib, dims, _random_gauge(torch, V, 1901))
+    g = torch.Generator(device="cuda").manual_seed(1902)
+    x = torch.view_as_complex(torch.randn(V, 12, n, 2, generator=g, device="cuda"))
+    y0, y = torch.empty_like(x), torch.empty_like(x)
+    ctx.dwc(y, x)
+    _set_walk(torch, ctx, dims, tmp_path / "tiled.txt", n, 1, (1, 1, 1, 1), 0, 0, 1)
+    ctx.dwc(y0, x)
+    torch.cuda.synchronize()
+    assert torch.equal(y, y0)
+    ctx.close()

@@ -198,3 +198,28 @@ def test_untuned_choice_costs_less_than_a_tenth_of_a_launch():
             f(C.byref(g), 12)
             best = min(best, time.perf_counter() - t)
         assert best * 1e6 < us
+
+
+# (lattice, Nrhs, the untuned choice), a case for each branch of the rules: the
+# operator with one and two right-hand sides per thread, one and two chunks
+# (16 right-hand sides and more a chunk store non-temporally), the odd and the
+# small batches, one right-hand side; the hop with one and two per thread
+UNTUNED_FINE = [
+    ((8, 8, 8, 8), 1, None), ((16, 16, 16, 32), 1, (1, (2, 2, 4, 4), 1)),
+    ((16, 16, 16, 16), 2, (1, (4, 4, 8, 2), 1)), ((16, 24, 20, 4), 6, (1, (4, 4, 4, 2), 1)),
+    ((12, 10, 6, 14), 5, None), ((12, 12, 12, 24), 7, (1, (3, 3, 6, 3), 1)),
+    ((12, 10, 6, 14), 12, None), ((8, 8, 8, 8), 12, (1, (2, 2, 4, 1), 1)),
+    ((16, 16, 16, 16), 12, (2, (4, 4, 4, 4), 1)), ((14, 15, 12, 20), 16, (2, (2, 5, 4, 5), 1)),
+    ((12, 10, 6, 14), 64, (1, (2, 2, 3, 7), 2)), ((12, 12, 12, 24), 64, (2, (3, 3, 3, 12), 2)),
+]
+UNTUNED_EO = [
+    ((12, 4, 8, 16), 64, None), ((16, 16, 16, 16), 16, (1, (2, 4, 4, 4))), ((16, 16, 16, 16), 24, (2, (2, 4, 4, 4))),
+    ((16, 16, 16, 32), 13, (1, (2, 4, 4, 8))), ((12, 12, 12, 24), 64, (1, (3, 3, 3, 12))),
+]
+
+
+def test_untuned_choices():
+    for dims, n, want in UNTUNED_FINE:
+        assert fine_default(dims, n) == want, (dims, n)
+    for dims, n, want in UNTUNED_EO:
+        assert eo_default(dims, n) == want, (dims, n)
