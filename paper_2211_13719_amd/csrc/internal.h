@@ -213,9 +213,9 @@ hipError_t launch_fine_f64(const Geom& g, int t_bc, int mode, double kappa, cons
 // Its constants are fitted to the times of some 5000 shapes on lattices from
 // 8^4 to 24^4 with 1 to 64 right-hand sides: there the shape it puts first
 // takes 4 % longer than the fastest on average (at most 23 %), and the first
-// 24 hold one within 1 % (the tuner times 16).
+// 24 hold one within 1 %.
 double staged_walk_cost(const Geom& g, const int tile[4], int nrhs, int R, int chunks, bool f64);
-// the count best of them, best first (R, T, chunks and walk set)
+// the count best of them that are worth timing, best first (R, T, chunks and walk set)
 std::vector<FineCfg> staged_walks(const Geom& g, int nrhs, bool f64, size_t count);
 // and of the checkerboard hop's walks that do (FP32), Ts in output sites
 double staged_eo_cost(const Geom& g, const int tile[4], int nrhs, int R);

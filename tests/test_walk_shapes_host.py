@@ -223,3 +223,32 @@ def test_untuned_choices():
         assert fine_default(dims, n) == want, (dims, n)
     for dims, n, want in UNTUNED_EO:
         assert eo_default(dims, n) == want, (dims, n)
+
+
+class _Vector(C.Structure):  # std::vector of a trivially copyable type, never freed here
+    _fields_ = [("begin", C.c_void_p), ("end", C.c_void_p), ("cap", C.c_void_p)]
+
+    def of(self, cls):
+        n = ((self.end or 0) - (self.begin or 0)) // C.sizeof(cls)
+        return list((cls * n).from_address(self.begin)) if n else []
+
+
+_staged_walks = _fn("_ZN4mrhs12staged_walksERKNS_4GeomEibm", _Vector, C.POINTER(Geom), C.c_int, C.c_bool, C.c_size_t)
+_staged_eo_walks = _fn("_ZN4mrhs15staged_eo_walksERKNS_4GeomEim", _Vector, C.POINTER(Geom), C.c_int, C.c_size_t)
+
+
+@pytest.mark.parametrize("dims", [(4, 4, 4, 4), (8, 8, 8, 8), (12, 10, 6, 14), (5, 7, 9, 11), (16, 16, 16, 32)])
+def test_tuner_times_only_shapes_near_the_best_estimate(dims):
+    """The walks in LDS that the tuner times: in order of their estimate, at most
+    as many as asked for, and none more than 1.25 times the first."""
+    g = geom(dims)
+    for n in (1, 6, 7, 12, 24, 64):
+        for f64 in (False, True):
+            costs = [_walk_cost(C.byref(g), w.T, n, w.R, w.chunks, f64)
+                     for w in _staged_walks(C.byref(g), n, f64, 16).of(FineCfg)]
+            assert len(costs) <= 16 and costs == sorted(costs)
+            assert not costs or (0 <= costs[0] and costs[-1] <= 1.25 * costs[0])
+        costs = [_eo_cost(C.byref(g), (C.c_int * 4)(*w.B, w.Ts), n, w.R)
+                 for w in _staged_eo_walks(C.byref(g), n, 16).of(EoWalk)]
+        assert len(costs) <= 16 and costs == sorted(costs)
+        assert not costs or (0 <= costs[0] and costs[-1] <= 1.25 * costs[0])
