@@ -40,6 +40,9 @@ __device__ __forceinline__ int site_agg(const AggGeom& a, int s) {
 // of a multiple of 16 sites, at most 4096; FP32 fields with either the FP32 basis on the
 // FP32 matrix cores or the packed BF16 basis on the BF16 ones.
 bool intergrid_mfma_supported(const AggGeom& a, int h, int nv);
+// whether the kernels that stage whole tiles in LDS are the faster ones for a
+// shape that they take
+bool intergrid_staged_leads(bool bf16, bool prolong, const AggGeom& a, int h, int nrhs);
 hipError_t launch_restrict_f32mfma(const AggGeom& a, int h, int nrhs, const void* W32, const void* f, void* y,
                                    hipStream_t s);
 hipError_t launch_prolong_f32mfma(const AggGeom& a, int h, int nrhs, const void* W32, const void* y, void* f,

@@ -775,11 +775,7 @@ bool staged(const AggGeom& a, int h, int nrhs, const void* W, const void* in, vo
   const int TS = h == 6 ? kTileSites<6> : kTileSites<16>;
   const int RT = TS * h * (BF16 && !PROLONG && nrhs <= 16 ? 2 : 1);
   if (nsa % TS || staged_lds(BF16, PROLONG, RT, nrhs, nsa) > 65536) return false;
-  // a handful of workgroups that walk whole aggregates leave the chip idle:
-  // the BF16 restriction of many columns then has twice as many workgroups
-  // above, one per column tile (8^4, 16 aggregates: 15.8 against 22.9 us at
-  // 64 RHS, 14.2 / 15.2 at 24; 12^3 x 16, 108 aggregates: 36.9 against 27.6 at 40)
-  if (BF16 && !PROLONG && nrhs > 16 && a.Vc <= 32) return false;
+  if (!intergrid_staged_leads(BF16, PROLONG, a, h, nrhs)) return false;
   if constexpr (PROLONG) {
     if (h == 6)
       *e = nrhs <= 32 ? launch_prolong_nt<6, 1, BF16>(a, nrhs, W, in, out, s)
@@ -803,6 +799,31 @@ __global__ __launch_bounds__(256) void pack_basis_bf16_kernel(const float2* __re
 }
 
 }  // namespace
+
+// More than 32 right-hand sides are two column tiles, which one staged workgroup
+// holds and two of the kernels above share: on few or short aggregates the
+// latter fill the chip better.  Measured over aggregates of 16 to 512 sites, 1 to
+// 512 of them, 33 to 64 right-hand sides, staged / other:
+//   FP32 restriction: 1.13 to 1.43 up to 16384 rows (sites times components), 0.5
+//   to 1.07 beyond, but 1.05 to 1.39 on up to 64 aggregates of at most 64 fine
+//   sites;
+//   BF16 restriction: 1.04 to 1.50 on 33 to 64 aggregates (the others have one
+//   workgroup per CU there, 0.88 at the least), as fast below, 0.46 to 1.11 above,
+//   with 48 and more right-hand sides on up to 128 aggregates of 64 fine sites
+//   1.07 to 1.17;
+//   aggregates of one tile (16 fine sites): restrictions 0.94 to 1.25, FP32
+//   prolongation 1.14 to 1.27 up to 64 of them and 0.72 to 0.90 beyond, BF16 0.95
+//   to 1.15; BF16 prolongation to up to 64 sites 0.98 to 1.21 on 64 to 144.
+// Up to 32 right-hand sides the staged kernels lead (0.2 to 1.08); the BF16
+// restriction of 17 to 32 on up to 32 aggregates is as fast either way.
+bool intergrid_staged_leads(bool bf16, bool prolong, const AggGeom& a, int h, int nrhs) {
+  const int nsa = a.b[0] * a.b[1] * a.b[2] * a.b[3];
+  const bool one_tile = h == 6 && nsa == 16, few_tiles = h == 6 && nsa <= 64;
+  if (nrhs <= 32) return !(bf16 && !prolong && nrhs > 16 && a.Vc <= 32);
+  if (prolong) return bf16 ? !(one_tile || (few_tiles && a.Vc >= 64 && a.Vc <= 144)) : !(one_tile && a.Vc <= 64);
+  if (one_tile || (few_tiles && a.Vc <= 64)) return false;
+  return bf16 ? a.Vc > (few_tiles && nsa > 32 && nrhs >= 48 ? 128 : 64) : (long)a.Vc * nsa * h > 16384;
+}
 
 bool intergrid_mfma_supported(const AggGeom& a, int h, int nv) {
   const int nsa = a.b[0] * a.b[1] * a.b[2] * a.b[3];

@@ -214,6 +214,20 @@ def test_restrict_prolong_tiles(gpu_lib, dims, block, level, nrhs):
     assert rel(host(fo), O.prolong_lowprec(b32, yc, dims, block)) < 2e-6
 
 
+@pytest.mark.parametrize("dims,block,level", [((12, 12, 12, 12), (4, 4, 4, 4), 0), ((10, 10, 6, 6), (2, 2, 2, 2), 1)])
+@pytest.mark.parametrize("nrhs", [33, 50, 64])
+def test_restrict_prolong_two_column_tiles(gpu_lib, dims, block, level, nrhs):
+    """Two column tiles in one workgroup, on the aggregates (81 and 225) where
+    these kernels are chosen: against the oracle with the bars of
+    test_restrict_prolong_tiles."""
+    from test_intergrid_rule_host import staged_leads
+
+    for prec in ("f32", "bf16"):
+        for prolong in (False, True):
+            assert staged_leads(prec, prolong, dims, block, 6 if level == 0 else 16, nrhs)
+    test_restrict_prolong_tiles(gpu_lib, dims, block, level, nrhs)
+
+
 def test_restrict_prolong_bf16_unsupported(gpu_lib):
     """n_v = 8 has no matrix-core intergrid path: a clear UNSUPPORTED error."""
     import torch
