@@ -2468,15 +2468,15 @@ struct Divisors {
   }
 };
 
-// The walk in LDS of the least estimated time below `limit`, the first of
-// equal ones; false if there is none.  Called by the first apply of a batch
+// The walk in LDS of the least estimated time below `limit`, the first of equal
+// ones, and that time in limit; false if there is none.  Called by the first apply of a batch
 // size, so it allocates nothing and leaves out what cannot win: a block whose
 // time is at least the best so far even with whole rounds and one long run.
 // 24^4 at 12 right-hand sides 18 us for the operator and 31 for the hop (every
 // shape costed and the hop's sorted: 107 and 218), 8^4 at 12 4.6 (9.7).
 // HOP: walks of the checkerboard hop, best.T[3] in output sites.
 template <bool HOP>
-bool best_staged_walk(const Geom& g, int nrhs, double limit, FineCfg& best) {
+bool best_staged_walk(const Geom& g, int nrhs, double& limit, FineCfg& best) {
   const Divisors dx(g.L[0], kStagedThreads * 4), dy(g.L[1], kStagedThreads * 4), dz(g.L[2], kStagedThreads * 4),
       dt(HOP ? g.L[3] / 2 : g.L[3], g.L[3]);
   bool found = false;
@@ -2528,7 +2528,8 @@ EoWalk eo_default(const Geom& g, int nrhs) {
   const double rows = (double)g.V * nrhs;
   for (int m = 0; m < 4; ++m)
     if (g.L[m] % 2) return out;
-  if (rows < 1 << 20 || !best_staged_walk<true>(g, nrhs, 1.55e-5 * rows, best)) return out;
+  double cost = 1.55e-5 * rows;
+  if (rows < 1 << 20 || !best_staged_walk<true>(g, nrhs, cost, best)) return out;
   out.on = 1;
   out.R = best.R;
   for (int m = 0; m < 3; ++m) out.B[m] = best.T[m];
@@ -2536,25 +2537,33 @@ EoWalk eo_default(const Geom& g, int nrhs) {
   return out;
 }
 
-// Against the tiled kernel, on 260 drawn lattices and batches without tuning:
-// even batches below 8 took 0.44 to 1.05 of its time, fields of 3e5 rows and
-// more of one right-hand side 0.57 to 1.06.  On smaller fields, whose rows the
-// tiled kernel finds in the caches, and for odd batches it took up to 1.3 where
-// the lattice's divisors cut it badly: there both times are estimated (fits
-// to the same draws, microseconds) and a lead is asked for.  One right-hand
-// side: 1.04 on average up to 5e4 sites, 0.97 at 16^3 x 32 and 0.54 at 24^4.
+// Against the tiled kernel, over 1600 drawn lattices and batches without tuning:
+// even batches below 8 took 0.44 to 1.14 of its time.  On fields of less than
+// 3e5 rows (sites times right-hand sides), which the tiled kernel finds in the
+// caches, and for odd batches the walk took up to 1.3 where the lattice's
+// divisors cut it badly, on larger ones up to 1.84 (13x10x9x13 at 20): both times
+// are estimated (fits to the same draws, microseconds) and a lead is asked for,
+// on larger fields more of one where chunks end within 128-byte lines.  That
+// leaves 7 of 475 large fields above 1.05, up to 1.23, and declines 18 where the
+// walk would gain 5 %.  One right-hand side: 1.04 on average up to 5e4 sites,
+// 0.97 at 16^3 x 32 and 0.54 at 24^4.
 FineCfg fine_default(const Geom& g, int nrhs) {
-  const double V = g.V, rows = V * nrhs;
-  double us = 1e30;  // what the walk has to beat; it takes 3.8 cost - 0.5
+  const double V = g.V, rows = V * nrhs, tiled = 1.9 + 90e-6 * rows + 359e-6 * V;
+  const bool large = nrhs % 2 == 0 && nrhs >= 8 && rows >= 3e5;
+  double cost = 1e30;  // what the walk's has to stay below
   if (nrhs == 1) {
     if (g.V < 1 << 17) return FineCfg{};
   } else if (nrhs % 2) {
-    us = 0.9 * (6.6 + 96.4e-6 * rows + 159e-6 * V);
-  } else if (nrhs >= 8 && rows < 3e5) {
-    us = 0.75 * (9.0 + 62.7e-6 * rows + 358e-6 * V);
+    cost = (0.9 * (6.6 + 96.4e-6 * rows + 159e-6 * V) + 0.5) / 3.8;
+  } else if (large) {
+    cost = (tiled - 1.6 - 32e-6 * rows) / 2.5;
+  } else if (nrhs >= 8) {
+    cost = (0.75 * (9.0 + 62.7e-6 * rows + 358e-6 * V) + 0.5) / 3.8;
   }
   FineCfg best;
-  if (!best_staged_walk<false>(g, nrhs, (us + 0.5) / 3.8, best)) return FineCfg{};
+  if (!best_staged_walk<false>(g, nrhs, cost, best)) return FineCfg{};
+  const bool part_lines = best.chunks > 1 && nrhs / best.chunks % 16;
+  if (large && part_lines && 2.5 * cost + 1.6 + 32e-6 * rows >= (rows > 2.5e6 ? 0.75 : 0.9) * tiled) return FineCfg{};
   // chunks of 16 and more write whole 128-byte lines, which need not stay in
   // the cache; non-temporal stores of less than a line cost up to a tenth
   best.nt = nrhs / best.chunks >= 16;

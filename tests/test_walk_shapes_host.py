@@ -169,9 +169,13 @@ def test_untuned_choice_is_that_of_the_full_search(dims):
                     c = _walk_cost(C.byref(g), (C.c_int * 4)(*T), n, R, chunks, False)
                     if 0 <= c < cost:
                         best, cost = (R, T, chunks), c
-        us = 3.8 * cost - 0.5
+        us, large = 3.8 * cost - 0.5, 2.5 * cost + 1.6 + 32e-6 * rows
+        tiled = 1.9 + 90e-6 * rows + 359e-6 * V
+        if best and best[2] > 1 and n // best[2] % 16:  # chunks that end within 128-byte lines
+            tiled *= 0.75 if rows > 2.5e6 else 0.9
         if ((n == 1 and V < 1 << 17) or (n > 1 and n % 2 and us >= 0.9 * (6.6 + 96.4e-6 * rows + 159e-6 * V))
-                or (n % 2 == 0 and n >= 8 and rows < 3e5 and us >= 0.75 * (9.0 + 62.7e-6 * rows + 358e-6 * V))):
+                or (n % 2 == 0 and n >= 8 and rows < 3e5 and us >= 0.75 * (9.0 + 62.7e-6 * rows + 358e-6 * V))
+                or (n % 2 == 0 and n >= 8 and rows >= 3e5 and large >= tiled)):
             best = None
         assert fine_default(dims, n) == best, n
         best, cost = None, 1.55e-5 * rows
@@ -252,3 +256,14 @@ def test_tuner_times_only_shapes_near_the_best_estimate(dims):
                  for w in _staged_eo_walks(C.byref(g), n, 16).of(EoWalk)]
         assert len(costs) <= 16 and costs == sorted(costs)
         assert not costs or (0 <= costs[0] and costs[-1] <= 1.25 * costs[0])
+
+
+@pytest.mark.parametrize("dims,n", [
+    # us of the tiled kernel and of the walk of the least estimated time
+    ((13, 10, 9, 13), 20),   # 33, 61
+    ((8, 9, 17, 13), 20),    # 36, 55
+    ((9, 19, 24, 11), 12),   # 72, 107
+    ((24, 19, 20, 22), 48),  # 887, 1171
+])
+def test_large_fields_that_are_cut_badly_run_the_tiled_kernel(dims, n):
+    assert fine_default(dims, n) is None
