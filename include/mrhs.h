@@ -124,8 +124,8 @@ mrhs_status mrhs_get_clover(mrhs_ctx ctx, void* A, mrhs_prec prec, int32_t on_de
  * (MRHS_F32 or MRHS_F64); they must not overlap.  The launch configuration
  * is the one mrhs_tune chose for nrhs (FP32: mrhs_get_tuning; FP64:
  * mrhs_get_f64_walk), else a default (FP32: the t-walk shape of the least
- * estimated time, or the tiled kernel where that is faster; FP64: the tiled kernel); every configuration gives the same
- * bits.  MRHS_ERR_STATE before links and clover are set. */
+ * estimated time, or the tiled kernel where that is expected to be faster;
+ * FP64: the tiled kernel); every configuration gives the same bits.  MRHS_ERR_STATE before links and clover are set. */
 mrhs_status mrhs_dwc_apply(mrhs_ctx ctx, void* out, const void* in, int32_t nrhs, mrhs_prec prec);
 /* mrhs_hop_apply: out = H in (hopping term only, Sec. 4 D_hop). */
 mrhs_status mrhs_hop_apply(mrhs_ctx ctx, void* out, const void* in, int32_t nrhs, mrhs_prec prec);
@@ -158,7 +158,7 @@ mrhs_status mrhs_hop_eo_apply(mrhs_ctx ctx, void* out, const void* in, int32_t n
  * selects the tiled kernel.  A walk whose block fits one workgroup keeps it in
  * LDS where that is estimated to be faster.  mrhs_tune chooses the shape by
  * timing (lattices with even extents); before either call it is the walk of
- * the least estimated time, or the tiled kernel on small lattices and those
+ * the least estimated time, or the tiled kernel on small fields and on lattices
  * whose extents cut badly into blocks.  The fields computed are bit-identical
  * either way.  An invalid shape gets MRHS_ERR_INVALID_ARG. */
 mrhs_status mrhs_set_eo_walk(mrhs_ctx ctx, int32_t nrhs, const int32_t* tile, int32_t rhs_per_thread);
@@ -531,11 +531,12 @@ mrhs_status mrhs_mg_solve(mrhs_mg mg, void* x, const void* b, int32_t nrhs, cons
  * nrhs are used without timing, new choices are appended.  Needs links and
  * clover.  Synchronises. */
 mrhs_status mrhs_tune(mrhs_ctx ctx, const int32_t* nrhs_list, int32_t count, const char* cache_path);
-/* mrhs_get_tuning: the configuration in use for nrhs: right-hand sides per
- * thread (0 = untuned default), tile[4] (0 = default tile; for the t-walk
- * kernel its spatial block and time slices per thread), variant = tile
- * order (0 lexicographic, 1 Morton) + 2 if compiled for at least 4
- * wavefronts per SIMD + 4 if the output is written with non-temporal
+/* mrhs_get_tuning: the configuration that mrhs_tune chose for nrhs: right-hand
+ * sides per thread (0 = not tuned: the launch is the default that
+ * mrhs_dwc_apply describes, which is not reported here), tile[4] (0 = not
+ * tuned; for the t-walk kernel its spatial block and time slices per thread),
+ * variant = tile order (0 lexicographic, 1 Morton) + 2 if compiled for at
+ * least 4 wavefronts per SIMD + 4 if the output is written with non-temporal
  * stores + 8 log2(RHS chunks) + 32 (workgroups-per-CU limit, 0 = none)
  * + 128 for the t-walk kernel, measured microseconds (0 if untuned).  Any
  * output pointer may be NULL. */

@@ -188,7 +188,7 @@ class Context:
         self._check(lib.mrhs_tune(self._h, arr, len(nrhs_list), path))
 
     def get_tuning(self, nrhs: int):
-        """(rhs_per_thread, tile, curve, microseconds) in use for nrhs (zeros when untuned)."""
+        """(rhs_per_thread, tile, curve, microseconds) that tune() chose for nrhs (zeros when untuned)."""
         r = C.c_int32()
         t = (C.c_int32 * 4)()
         cv = C.c_int32()

@@ -224,13 +224,6 @@ mrhs_status ensure_clover_inverse(mrhs_ctx ctx) {
   return MRHS_OK;
 }
 
-// Site traversal of the fine kernels.  Sites are grouped in tiles of extent
-// T; tiles are visited t-row by t-row (the tile index along t outermost, so
-// that with Lt / T_t = 8 each XCD, which takes a contiguous eighth of the
-// traversal, works on its own slab of time slices), and within a t-row
-// either lexicographically (curve 0) or along a Morton curve in (x, y, z)
-// (curve 1), which keeps tiles that are neighbours in y and z close in time.
-// Sites inside a tile are lexicographic.
 const FineCfg* fine_config(mrhs_ctx ctx, int nrhs) {
   if (ctx->fine_cfg[nrhs].R > 0) return &ctx->fine_cfg[nrhs];
   std::call_once(ctx->fine_auto_once[nrhs], [&] { ctx->fine_auto[nrhs] = fine_default(ctx->g, nrhs); });
@@ -243,6 +236,13 @@ const EoWalk* eo_config(mrhs_ctx ctx, int nrhs) {
   return &ctx->eo_auto[nrhs];
 }
 
+// Site traversal of the fine kernels.  Sites are grouped in tiles of extent
+// T; tiles are visited t-row by t-row (the tile index along t outermost, so
+// that with Lt / T_t = 8 each XCD, which takes a contiguous eighth of the
+// traversal, works on its own slab of time slices), and within a t-row
+// either lexicographically (curve 0) or along a Morton curve in (x, y, z)
+// (curve 1), which keeps tiles that are neighbours in y and z close in time.
+// Sites inside a tile are lexicographic.
 const int* fine_order_table(mrhs_ctx ctx, const int T[4], int curve) {
   std::array<int, 5> key{T[0], T[1], T[2], T[3], curve};
   for (auto& o : ctx->orders)

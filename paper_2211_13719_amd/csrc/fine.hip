@@ -963,7 +963,7 @@ __device__ __forceinline__ void staged_walk(const Geom& g, int nrhs, T kappa, co
                            : hlk + (fX + lz * w.B[0] + lx) * 10 + 1;
   const cplx<T>* lzb = izb ? lk + (sb + (lz > 0 ? -1 : w.B[2] - 1) * w.B[0] * w.B[1]) * 36 + 18
                            : hlk + (fX + fY + ly * w.B[0] + lx) * 10;
-  // this thread's share of the block's links and clover blocks: 16-byte words
+  // this thread's share of the block's links: 16-byte words
   // p = tid + j TH of the bs UPS words, and entries of the backward halo links
   unsigned lo[NL], ho[NH];
 #pragma unroll
@@ -1188,14 +1188,11 @@ __global__ __launch_bounds__(256, 1) void fine_walk_f64_kernel(Geom g, int nrhs,
   staged_walk<double, 1, LINKS, false>(g, nrhs, kappa, U, A, in, out, w, nt_out, nullptr);
 }
 
-// Shape of a staged walk for tile T = (Bx, By, Bz, Ts); links = which of the
-// two instances it takes.  False where it does not fit: the tile does not
-// divide the lattice; a block one site wide that does not span the lattice
-// (its sites would have two neighbours outside in one dimension); more
-// threads, link words or LDS than one workgroup has; a time slice beyond the
-// 32-bit byte offsets.
-bool staged_dims(const Geom& g, const int T[4], int nrhs, int R, int chunks, int real_bytes, int max_threads,
-                 StagedWalk& w) {
+// Shape of a staged walk for tile T = (Bx, By, Bz, Ts).  False where it does not
+// fit: the tile does not divide the lattice; a block one site wide that does not
+// span the lattice (its sites would have two neighbours outside in one
+// dimension); more threads than one workgroup has.
+bool staged_dims(const Geom& g, const int T[4], int nrhs, int R, int chunks, int max_threads, StagedWalk& w) {
   for (int m = 0; m < 4; ++m)
     if (T[m] < 1 || g.L[m] % T[m]) return false;
   if (chunks < 1 || nrhs % chunks || (nrhs / chunks) % R) return false;
@@ -1218,7 +1215,10 @@ bool staged_dims(const Geom& g, const int T[4], int nrhs, int R, int chunks, int
   return w.per * 8 <= 0x7fffffffL;
 }
 
-// slices: time slices whose links are staged together; variants: instances there are
+// Its LDS, and in `links` which of the instances there are (variants) it takes,
+// by the link words per thread; slices: time slices whose links are staged
+// together.  False where a workgroup has too few threads or too little LDS, or a
+// time slice lies beyond the 32-bit byte offsets.
 bool staged_links(const Geom& g, int slices, int nrhs, int R, int real_bytes, int variants, StagedWalk& w, int& links) {
   const int words = slices * w.bs * 36 * 2 * real_bytes / 16;
   int halo = 0;
@@ -1236,7 +1236,7 @@ bool staged_links(const Geom& g, int slices, int nrhs, int R, int real_bytes, in
 
 bool staged_shape(const Geom& g, const int T[4], int nrhs, int R, int chunks, int real_bytes, int max_threads,
                   StagedWalk& w, int& links) {
-  return staged_dims(g, T, nrhs, R, chunks, real_bytes, max_threads, w) &&
+  return staged_dims(g, T, nrhs, R, chunks, max_threads, w) &&
          staged_links(g, 1, nrhs, R, real_bytes, R > 1 ? 1 : 3, w, links);
 }
 
@@ -2059,7 +2059,7 @@ bool staged_eo_shape(const Geom& g, const int B[3], int Ts, int nrhs, int R, Sta
     if (g.L[m] % 2) return false;
   if (Ts < 1 || (long)B[0] * B[1] * B[2] < kEoWalkMinBlock) return false;
   for (int chunks = 1; chunks <= 4; chunks *= 2) {
-    if (!staged_dims(g, T, nrhs, R, chunks, 4, kStagedThreads, w) ||
+    if (!staged_dims(g, T, nrhs, R, chunks, kStagedThreads, w) ||
         !staged_links(g, 2, nrhs, R, 4, R == 2 ? 1 : 2, w, links))
       continue;
     w.lds += (unsigned)(w.threads * (R == 2 ? kEoPriv<2, true> : 0) * 16);
