@@ -125,7 +125,8 @@ mrhs_status mrhs_get_clover(mrhs_ctx ctx, void* A, mrhs_prec prec, int32_t on_de
  * is the one mrhs_tune chose for nrhs (FP32: mrhs_get_tuning; FP64:
  * mrhs_get_f64_walk), else a default (FP32: the t-walk shape of the least
  * estimated time, or the tiled kernel where that is expected to be faster;
- * FP64: the tiled kernel); every configuration gives the same bits.  MRHS_ERR_STATE before links and clover are set. */
+ * FP64: the tiled kernel); every configuration gives the same bits.
+ * MRHS_ERR_STATE before links and clover are set. */
 mrhs_status mrhs_dwc_apply(mrhs_ctx ctx, void* out, const void* in, int32_t nrhs, mrhs_prec prec);
 /* mrhs_hop_apply: out = H in (hopping term only, Sec. 4 D_hop). */
 mrhs_status mrhs_hop_apply(mrhs_ctx ctx, void* out, const void* in, int32_t nrhs, mrhs_prec prec);

@@ -592,6 +592,41 @@ def test_coarse_half_column_loads(gpu_lib, nrhs, fmt):
     assert rel(host(hop) + host(own), want[ev]) < 1e-6
 
 
+@pytest.mark.parametrize("nrhs", [5, 16, 24, 40])
+def test_a_column_of_nan_and_infinity_stays_alone(gpu_lib, nrhs):
+    """NaN and infinities in one right-hand side leave the bits of the others as
+    they are without them: staged transfers, the coarse stencils with half and
+    whole columns, the MR solve whose steps sum their own lengths."""
+    import torch
+
+    ctx, mg = make_mg(gpu_lib, (12, 12, 12, 12), [(4, 4, 4, 4)], [16])
+    V, Vc, nc = mg.volume[0], mg.volume[1], mg.ncomp[0]
+    mg.set_basis(0, synth.gaussian_vectors(V, 16, nc, 81) / np.sqrt(2.0 * nc * 256))
+    mg.set_blocks(1, synth.gaussian_blocks(Vc, 32, 82, shift=24.0))
+    fine = dev(synth.coarse_source(V, nc, nrhs, 83, np.complex64))
+    coarse = dev(synth.coarse_source(Vc, 32, nrhs, 84, np.complex64))
+    bad = nrhs - 2
+    calls = {}
+    for prec in ("f32", "bf16"):
+        calls["restrict " + prec] = (lambda y, x, p=prec: mg.restrict(0, y, x, p), coarse, fine)
+        calls["prolong " + prec] = (lambda y, x, p=prec: mg.prolong(0, y, x, p), fine, coarse)
+    for prec in ("bf16", "f16"):
+        calls["stencil " + prec] = (lambda y, x, p=prec: mg.coarse_apply(1, y, x, p), coarse, coarse)
+    calls["mr"] = (lambda y, x: mg.coarse_mr_solve(1, y, x, 6, "bf16"), coarse, coarse)
+    others = [k for k in range(nrhs) if k != bad]
+    for name, (call, like, x) in calls.items():
+        out = []
+        for values in (None, (complex(np.nan, 1.0), complex(np.inf, -np.inf))):
+            y, xx = torch.empty_like(like), x.clone()
+            if values:
+                xx[::2, :, bad], xx[1::2, :, bad] = values
+            call(y, xx)
+            out.append(y)
+        torch.cuda.synchronize()
+        assert not torch.isfinite(torch.view_as_real(out[1][:, :, bad])).all(), name
+        assert torch.equal(out[0][:, :, others], out[1][:, :, others]), name
+
+
 def test_coarse_apply_nb8_valu(gpu_lib):
     import torch
 
