@@ -251,6 +251,7 @@ mrhs_status mrhs_tune(mrhs_ctx ctx, const int32_t* nrhs_list, int32_t count, con
     };
     best.R = (n % 2 == 0) ? 2 : 1;
     best.us = 1e30f;
+    FineCfg tiled = best;  // the fastest tile
     auto scan_tiles = [&](const FineCfg& base) {
       for (const auto& t : tile_candidates(ctx->g)) {
         for (int curve : {0, 1}) {
@@ -260,6 +261,7 @@ mrhs_status mrhs_tune(mrhs_ctx ctx, const int32_t* nrhs_list, int32_t count, con
           e = time_cfg(cfg);
           if (e != hipSuccess) return;
           if (cfg.us < best.us) best = cfg;
+          if (cfg.us < tiled.us) tiled = cfg;
         }
       }
     };
@@ -287,6 +289,16 @@ mrhs_status mrhs_tune(mrhs_ctx ctx, const int32_t* nrhs_list, int32_t count, con
         if (e == hipSuccess && cfg.us < best.us) best = cfg;
       }
     if (e == hipSuccess) scan_tiles(plain);
+    // The stages below move on from the leader alone: where that is a walk, the
+    // tiled kernel's other right-hand sides per thread are timed here (11x7x9x18
+    // at 2: the walk 17 us, tiled with two per thread 18, with one 13).
+    for (int v : {1, 2, 4}) {
+      if (!best.walk || n % v || v == plain.R || e != hipSuccess) continue;
+      FineCfg cfg = tiled;
+      cfg.R = v;
+      e = time_cfg(cfg);
+      if (e == hipSuccess && cfg.us < best.us) best = cfg;
+    }
     if (e == hipSuccess) scan_walks(plain);
     // stages: 0 RHS per thread, 1 RHS chunks, 2 workgroups per CU, 3 register budget, 4 store kind
     for (int stage = 0; stage < 5 && e == hipSuccess; ++stage) {

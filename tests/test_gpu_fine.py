@@ -503,3 +503,35 @@ def test_untuned_choice_is_the_tiled_result(gpu_lib, tmp_path, dims, n, choice):
     torch.cuda.synchronize()
     assert torch.equal(y, y0)
     ctx.close()
+
+
+def test_tuner_tries_one_rhs_per_thread_beside_a_walk(gpu_lib, tmp_path):
+    """11x7x9x18 at two right-hand sides: a walk leads the tiled kernel with two
+    per thread (17 against 18 us), and the tiled kernel with one (11 us among
+    others) leads both; the tuned operator is within 1.2 of it."""
+    import torch
+
+    dims, n = (11, 7, 9, 18), 2
+    V = int(np.prod(dims))
+    ctx = _ctx(gpu_lib, dims, _random_gauge(torch, V, 2001))
+    g = torch.Generator(device="cuda").manual_seed(2002)
+    x = torch.view_as_complex(torch.randn(V, 12, n, 2, generator=g, device="cuda"))
+    y = torch.empty_like(x)
+
+    def us():
+        start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        best = 1e9
+        for _ in range(8):
+            start.record()
+            for _ in range(50):
+                ctx.dwc(y, x)
+            end.record()
+            end.synchronize()
+            best = min(best, start.elapsed_time(end) * 20)
+        return best
+
+    ctx.tune([n])
+    tuned = us()
+    _set_walk(torch, ctx, dims, tmp_path / "tiled.txt", n, 1, (1, 1, 1, 1), 0, 0, 1)
+    assert tuned < 1.2 * us()
+    ctx.close()
