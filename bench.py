@@ -92,7 +92,7 @@ FINE_SOURCES = ("fine.hip", "internal.h", "api.hip")
 # it only while the kernel name, sources and configurations still match.
 FINE_TRAFFIC = {
     "kernel": "fine_walk_kernel<2, 0, false>",
-    "sources": "c79a72849657170f",
+    "sources": "2c84746d9d546f19",
     "configs": {"12": [2, [3, 3, 8, 6], 128], "24": [2, [6, 3, 2, 12], 132], "48": [2, [3, 3, 2, 24], 132],
                 "64": [2, [4, 2, 2, 12], 132]},
     "bytes_per_launch": 4.692e9,

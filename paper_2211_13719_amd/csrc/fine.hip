@@ -1277,7 +1277,8 @@ struct WalkFit {
 constexpr WalkFit kHopFit = {{2.09, 2.74}, 3.03, 0.905, 0.032, 0.094, 5.04, 29.4e-6, {7.34, 9.32}, 0.885, 10.6, 25.5e-6, 206e-6, 2, 3};
 constexpr WalkFit kF64Fit = {{0.394, 0.0}, 6.26, 0.563, 0.209, 0.077, 4.16, 101e-6, {3.63, 0.0}, 1.30, 2.84, 86.9e-6, 166e-6, 1, 1};
 
-// w.lds, w.Ts and w.total_wg are the launch's; words: 16-byte link words it stages; open_wg: the open walk's workgroups
+// w.lds, w.Ts and w.total_wg are the launch's; words: 16-byte link words it
+// stages; open_wg: the open walk's workgroups
 bool lds_is_faster(const Geom& g, const WalkFit& f, const StagedWalk& w, int R, int nrhs, long words, long open_wg) {
   const int waves = w.threads / 64;
   const long res = std::max<long>(1, std::min({160 * 1024L / w.lds, 4L * f.res / waves, (w.total_wg + 255) / 256}));
@@ -2380,18 +2381,34 @@ double staged_cost_bound(const StagedWalk& w, int R, long slices) {
 double staged_walk_cost(const Geom& g, const int tile[4], int nrhs, int R, int chunks, bool f64) {
   StagedWalk w;
   int links = 0;
-  if (f64 ? !f64_in_lds(g, tile, nrhs, w, links) : !f32_in_lds(g, tile, nrhs, R, chunks, w, links)) return -1.0;
+  if (f64 ? !staged_shape_f64(g, tile, nrhs, w, links)
+          : !staged_shape(g, tile, nrhs, R, chunks, 4, kStagedThreads, w, links))
+    return -1.0;
   return staged_cost(w, R, f64);
 }
 
 double staged_eo_cost(const Geom& g, const int tile[4], int nrhs, int R) {
   StagedWalk w;
   int links = 0;
-  return eo_in_lds(g, tile, tile[3], nrhs, R, w, links) ? staged_cost(w, R, false) : -1.0;
+  return staged_eo_shape(g, tile, tile[3], nrhs, R, w, links) ? staged_cost(w, R, false) : -1.0;
+}
+
+bool walk_in_lds(const Geom& g, const int tile[4], int nrhs, int R, int chunks, bool f64) {
+  StagedWalk w;
+  int links = 0;
+  return f64 ? f64_in_lds(g, tile, nrhs, w, links) : f32_in_lds(g, tile, nrhs, R, chunks, w, links);
+}
+
+bool eo_walk_in_lds(const Geom& g, const int tile[4], int nrhs, int R) {
+  StagedWalk w;
+  int links = 0;
+  return eo_in_lds(g, tile, tile[3], nrhs, R, w, links);
 }
 
 // The first `count` by estimated time of those within kStagedSpread of the
 // first: on 146 lattices and batches the fastest of 16 was always among them.
+// Shapes that the rule leaves to the open walk are worth timing there (hop: over
+// those draws the best of all takes 0.97 of the best in LDS).
 constexpr double kStagedSpread = 1.25;
 template <typename C>
 std::vector<C> cheapest(std::vector<std::pair<double, C>>& all, size_t count) {

@@ -205,9 +205,8 @@ bool launch_fine_residual_f32(const Geom& g, float kappa, const void* U, const v
 hipError_t launch_fine_f64(const Geom& g, int t_bc, int mode, double kappa, const void* U,
                            const void* A, const void* in, void* out, int nrhs, hipStream_t s,
                            const F64Walk* fw = nullptr);
-// Estimated time (arbitrary unit) of the walk of tile (Bx, By, Bz, Ts) that
-// keeps its block in LDS, -1 for a shape that runs the walk without (it does
-// not fit, or is expected to be slower there): the rounds of workgroups
+// Estimated time (arbitrary unit) of the walk of tile (Bx, By, Bz, Ts) with its
+// block in LDS, -1 where that does not fit: the rounds of workgroups
 // that the registers and LDS of 256 CUs admit together, times the wavefronts
 // per SIMD in one, times the slices, times the rows from outside the block.
 // Its constants are fitted to the times of some 5000 shapes on lattices from
@@ -215,10 +214,14 @@ hipError_t launch_fine_f64(const Geom& g, int t_bc, int mode, double kappa, cons
 // takes 4 % longer than the fastest on average (at most 23 %), and the first
 // 24 hold one within 1 %.
 double staged_walk_cost(const Geom& g, const int tile[4], int nrhs, int R, int chunks, bool f64);
+// whether that walk runs with its block in LDS: it fits and is expected to be
+// faster there
+bool walk_in_lds(const Geom& g, const int tile[4], int nrhs, int R, int chunks, bool f64);
 // the count best of them that are worth timing, best first (R, T, chunks and walk set)
 std::vector<FineCfg> staged_walks(const Geom& g, int nrhs, bool f64, size_t count);
-// and of the checkerboard hop's walks that do (FP32), Ts in output sites
+// and the checkerboard hop's (FP32), Ts in output sites
 double staged_eo_cost(const Geom& g, const int tile[4], int nrhs, int R);
+bool eo_walk_in_lds(const Geom& g, const int tile[4], int nrhs, int R);
 std::vector<EoWalk> staged_eo_walks(const Geom& g, int nrhs, size_t count);
 // the untuned checkerboard hop (FP32)
 EoWalk eo_default(const Geom& g, int nrhs);

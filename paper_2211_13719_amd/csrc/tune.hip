@@ -95,9 +95,9 @@ std::vector<std::array<int, 4>> walk_candidates(const Geom& g) {
   return out;
 }
 
-// Walks that keep their block in LDS are timed by estimate instead, the first of
-// the FP32 operator and the hop, and of the FP64 operator (where 8 lose 1 % at
-// most against 16).  A candidate of the lists above that runs there is skipped.
+// Walks whose block fits LDS are timed by estimate instead, the first of the FP32
+// operator and the hop, and of the FP64 operator (where 8 lose 1 % at most
+// against 16).  A candidate of the lists above that runs there is skipped.
 constexpr size_t kStagedTimed = 16, kStagedTimed64 = 8;
 // a first time this much longer than the best so far ends a candidate
 constexpr float kTuneGiveUp = 1.25f;
@@ -275,7 +275,7 @@ mrhs_status mrhs_tune(mrhs_ctx ctx, const int32_t* nrhs_list, int32_t count, con
           cfg.walk = 1;
           cfg.curve = 0;
           for (int m = 0; m < 4; ++m) cfg.T[m] = t[m];
-          if (cfg.occ == 0 && staged_walk_cost(ctx->g, cfg.T, n, R, cfg.chunks, false) >= 0.0) continue;
+          if (cfg.occ == 0 && walk_in_lds(ctx->g, cfg.T, n, R, cfg.chunks, false)) continue;
           e = time_cfg(cfg);
           if (e != hipSuccess) return;
           if (cfg.us < best.us) best = cfg;
@@ -423,7 +423,7 @@ mrhs_status mrhs_tune(mrhs_ctx ctx, const int32_t* nrhs_list, int32_t count, con
         for (int m = 0; m < 3; ++m) w.B[m] = b[m];
         w.Ts = ts0;
         const int tile[4] = {b[0], b[1], b[2], ts0};
-        if (staged_eo_cost(ctx->g, tile, n, n % 2 == 0 ? 2 : 1) < 0.0) consider(w);
+        if (!eo_walk_in_lds(ctx->g, tile, n, n % 2 == 0 ? 2 : 1)) consider(w);
       }
       if (best.on) {
         const EoWalk base = best;
@@ -498,7 +498,7 @@ mrhs_status mrhs_tune(mrhs_ctx ctx, const int32_t* nrhs_list, int32_t count, con
         std::vector<std::array<int, 4>> tiles;
         for (const FineCfg& c : staged_walks(ctx->g, n, true, kStagedTimed64)) tiles.push_back({c.T[0], c.T[1], c.T[2], c.T[3]});
         for (const auto& t : walk_candidates(ctx->g))
-          if (staged_walk_cost(ctx->g, t.data(), n, 1, 1, true) < 0.0) tiles.push_back(t);
+          if (!walk_in_lds(ctx->g, t.data(), n, 1, 1, true)) tiles.push_back(t);
         for (const auto& t : tiles) {
           if (e != hipSuccess) break;
           const int tile[4] = {t[0], t[1], t[2], t[3]};

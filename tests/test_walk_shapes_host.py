@@ -34,18 +34,22 @@ _walk_cost = _fn("_ZN4mrhs16staged_walk_costERKNS_4GeomEPKiiiib", C.c_double, C.
                  C.c_int, C.c_int, C.c_int, C.c_bool)
 _eo_cost = _fn("_ZN4mrhs14staged_eo_costERKNS_4GeomEPKiii", C.c_double, C.POINTER(Geom), C.POINTER(C.c_int), C.c_int,
                C.c_int)
+_walk_in_lds = _fn("_ZN4mrhs11walk_in_ldsERKNS_4GeomEPKiiiib", C.c_bool, C.POINTER(Geom), C.POINTER(C.c_int), C.c_int,
+                   C.c_int, C.c_int, C.c_bool)
+_eo_in_lds = _fn("_ZN4mrhs14eo_walk_in_ldsERKNS_4GeomEPKiii", C.c_bool, C.POINTER(Geom), C.POINTER(C.c_int), C.c_int,
+                 C.c_int)
 
 
 def fine_in_lds(dims, n, R, tile, chunks=1):
-    return _walk_cost(C.byref(geom(dims)), (C.c_int * 4)(*tile), n, R, chunks, False) >= 0
+    return _walk_in_lds(C.byref(geom(dims)), (C.c_int * 4)(*tile), n, R, chunks, False)
 
 
 def f64_in_lds(dims, n, tile):
-    return _walk_cost(C.byref(geom(dims)), (C.c_int * 4)(*tile), n, 1, 1, True) >= 0
+    return _walk_in_lds(C.byref(geom(dims)), (C.c_int * 4)(*tile), n, 1, 1, True)
 
 
 def eo_in_lds(dims, n, R, tile):
-    return _eo_cost(C.byref(geom(dims)), (C.c_int * 4)(*tile), n, R) >= 0
+    return _eo_in_lds(C.byref(geom(dims)), (C.c_int * 4)(*tile), n, R)
 
 
 # Shapes that keep their block in LDS, at the edges of what it takes; the GPU
@@ -167,7 +171,7 @@ def test_untuned_choice_is_that_of_the_full_search(dims):
                     continue
                 for T in _tiles(dims, dims[3], 512 * R * chunks // n):
                     c = _walk_cost(C.byref(g), (C.c_int * 4)(*T), n, R, chunks, False)
-                    if 0 <= c < cost:
+                    if 0 <= c < cost and fine_in_lds(dims, n, R, T, chunks):
                         best, cost = (R, T, chunks), c
         us, large = 3.8 * cost - 0.5, 2.5 * cost + 1.6 + 32e-6 * rows
         tiled = 1.9 + 90e-6 * rows + 359e-6 * V
@@ -183,7 +187,7 @@ def test_untuned_choice_is_that_of_the_full_search(dims):
             for R in (1, 2):
                 for T in _tiles(dims, dims[3] // 2, 2048 * R // n) if n % R == 0 else []:
                     c = _eo_cost(C.byref(g), (C.c_int * 4)(*T), n, R)
-                    if 0 <= c < cost:
+                    if 0 <= c < cost and eo_in_lds(dims, n, R, T):
                         best, cost = (R, T), c
         assert eo_default(dims, n) == best, n
 
@@ -243,7 +247,7 @@ _staged_eo_walks = _fn("_ZN4mrhs15staged_eo_walksERKNS_4GeomEim", _Vector, C.POI
 
 @pytest.mark.parametrize("dims", [(4, 4, 4, 4), (8, 8, 8, 8), (12, 10, 6, 14), (5, 7, 9, 11), (16, 16, 16, 32)])
 def test_tuner_times_only_shapes_near_the_best_estimate(dims):
-    """The walks in LDS that the tuner times: in order of their estimate, at most
+    """The walks that fit LDS which the tuner times: in order of their estimate, at most
     as many as asked for, and none more than 1.25 times the first."""
     g = geom(dims)
     for n in (1, 6, 7, 12, 24, 64):
