@@ -427,7 +427,10 @@ __global__ __launch_bounds__(256) void prolong_f32_kernel(AggGeom a, int h, int 
 // LDS.  Prolongation writes its tile to LDS too, so that whole rows go out as
 // 16-byte words.  All column tiles of a site belong to one workgroup, so the
 // basis is read once for up to 64 right-hand sides.
-// 24^4 with 4^4 aggregates, restrict / prolong in us, before -> now:
+// 24^4 with 4^4 aggregates, restrict / prolong in us, each in a loop of its own
+// (in turn a prolongation is up to an eighth faster and the restriction after it
+// up to a fifth slower, which then waits for what the first left in the caches
+// to be written back; pair by pair 516 and 412 at 24), before -> now:
 //   FP32 at 12 RHS 362 / 332 -> 219 / 213, at 24 400 / 382 -> 245 / 265 (5.2 and
 //   4.8 TB/s), at 48 710 / 612 -> 452 / 503;
 //   BF16 at 12 RHS 180 / 249 -> 117 / 143, at 24 227 / 319 -> 187 / 208 (5.5 and
